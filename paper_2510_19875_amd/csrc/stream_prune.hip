@@ -29,10 +29,14 @@ namespace stream {
 // spills, and a level's first MFMAs start after half as many bytes have arrived).  Used for short
 // lists, where a level has a handful of tiles: measured 3-5 % faster there, 3-4 % slower on long
 // lists.  (A third wavefront per SIMD would fit only with ~30 spilled registers: slower.)
-template <bool BF16, int D, int MB, int NG, int WPR, int OCC, bool MULTI, bool ARB = false, int KS = 1>
+// SPLIT: the four wavefronts of a workgroup share one row, each holding its whole Q tile: wavefront w scores
+// every fourth block of a level's list from the w-th on, all four read the level's scores and run the
+// (identical) selection.  For launches of few rows, which last as long as their longest row.
+template <bool BF16, int D, int MB, int NG, int WPR, int OCC, bool MULTI, bool ARB = false, int KS = 1, bool SPLIT = false>
 __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
 {
-    static_assert(KS == 1 || WPR == 1, "sub-tiles only in the one-wavefront-per-row form");
+    static_assert((KS == 1 && !SPLIT) || WPR == 1, "only in the form in which a wavefront scores whole blocks");
+    constexpr bool SHARED = WPR == 4 || SPLIT;            // the workgroup's four wavefronts work on one row
     constexpr int ES = BF16 ? 2 : 4;
     constexpr int FR = D * ES / 32;                       // fragments per 32-token group
     // bf16 tiles are multiplied with 16x16x32 MFMAs (S16): under the power limit that governs a
@@ -65,7 +69,7 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
     int kvh, slot;
     if (!wg_decode(p.map, blockIdx.x, kvh, slot)) return;
     const long long rows_per_kv = (long long)p.NB * p.g;
-    const long long rk = WPR == 1 ? (long long)slot * 4 + wave : (long long)slot;
+    const long long rk = !SHARED ? (long long)slot * 4 + wave : (long long)slot;
     if (rk >= rows_per_kv) return;
     const int gb = p.NB - 1 - (int)(rk / p.g);            // long rows first
     const int h = kvh * p.g + (int)(rk % p.g);
@@ -243,8 +247,10 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
         wave_sync();
 
         uint4 kf[CG][KF];
-        if (nt > 0) {
-            const int r0 = __builtin_amdgcn_readfirstlane(s_rep[wave][0]);
+        const int t_first = SPLIT ? wave : 0;             // this wavefront's blocks of the list
+        const int n_mine = SPLIT ? (nt - wave + 3) >> 2 : nt;
+        if (n_mine > 0) {
+            const int r0 = __builtin_amdgcn_readfirstlane(s_rep[wave][t_first]);
             // same order as the refills in the loop below: waits count loads in issue order
 #pragma unroll
             for (int fr = 0; fr < KF; ++fr)
@@ -255,13 +261,13 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
                 }
         }
         float mx = -INFINITY;
-        for (int u = 0; u < nt * KS; ++u) {
+        for (int u = 0; u < n_mine * KS; ++u) {
             // sub-tile sk of the t-th block to score; the one after it (the last repeats itself)
-            const int t = u / KS, sk = u % KS;
-            const bool more = u + 1 < nt * KS;
+            const int t = SPLIT ? wave + 4 * (u / KS) : u / KS, sk = u % KS;
+            const bool more = u + 1 < n_mine * KS;
             const int un = more ? u + 1 : u;
             const int r = __builtin_amdgcn_readfirstlane(s_rep[wave][t]);
-            const unsigned nxt = (unsigned)__builtin_amdgcn_readfirstlane(s_rep[wave][un / KS]) * (unsigned)TILE_BYTES +
+            const unsigned nxt = (unsigned)__builtin_amdgcn_readfirstlane(s_rep[wave][SPLIT ? wave + 4 * (un / KS) : un / KS]) * (unsigned)TILE_BYTES +
                                  (unsigned)(un % KS) * (unsigned)(NG * GROUP_BYTES);
             // after the level's last tile there is nothing to fetch ahead: the refills then go
             // through a resource of zero bytes, which answers every load with zeros without a
@@ -349,19 +355,19 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
             }
             if (sk == KS - 1) {
                 mx = wave_max(mx);
-                if (lane == 0) s_sc[wave][t] = mx;
+                if (lane == 0) s_sc[SPLIT ? 0 : wave][t] = mx;
                 mx = -INFINITY;
             }
         }
         tiles_done += (unsigned long long)nt;
         wave_sync();
-        if constexpr (WPR == 4) __syncthreads();
+        if constexpr (SHARED) __syncthreads();
 
         auto tile_score = [&](int t) -> float {
             if constexpr (WPR == 4)
                 return fmaxf(fmaxf(s_sc[0][t], s_sc[1][t]), fmaxf(s_sc[2][t], s_sc[3][t]));
             else
-                return s_sc[wave][t];
+                return s_sc[SPLIT ? 0 : wave][t];
         };
         float s0 = -INFINITY, s1 = -INFINITY;
         if (v0) s0 = need0 ? tile_score(pos0) : (hit0 ? c0 : sc);
@@ -372,7 +378,7 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
         }
         // the four wavefronts of a row must all have read this level's tile scores before any of
         // them writes the next level's
-        if constexpr (WPR == 4) __syncthreads();
+        if constexpr (SHARED) __syncthreads();
 
         // ---- top-k of the 2k branch scores (ties to the lower position): see select_topk_wave
         const float sel_s[2] = {s0, s1};
@@ -384,7 +390,7 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
         const int before = lanes_below(kb0) + lanes_below(kb1);
         const int p0 = before, p1 = before + (keep0 ? 1 : 0);
         const int newcnt = __popcll(kb0) + __popcll(kb1);
-        const bool writer = WPR == 1 || wave == 0;
+        const bool writer = !SHARED || wave == 0;
 
         if (p.trace && writer) {
             int *tr = p.trace + (((long long)(level - 1) * p.H * n_k * p.NB + row) * p.kmax) * 2;
@@ -438,7 +444,7 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
     }
     if constexpr (MULTI) wave_sync();     // the last level's cache entries, before the next k reads them
     }
-    if (p.tiles && (WPR == 1 || wave == 0) && lane == 0) atomicAdd(p.tiles, tiles_done);
+    if (p.tiles && (!SHARED || wave == 0) && lane == 0) atomicAdd(p.tiles, tiles_done);
 }
 
 struct PruneWorkspace {
@@ -477,13 +483,35 @@ typedef void (*level_fn)(const PruneParams);
 // Lists this short take the two-sub-tile form (KS = 2) of the 64 x 64 bf16 kernel.
 constexpr int kShortListTopk = 8;
 
+// Whether the four wavefronts of a workgroup share a row: few rows per block kept (a level offers about as
+// many independent tiles as blocks are kept, and every sharing wavefront repeats the row's decode, Q tile and
+// selections).  us, own row / shared row: 32-token blocks 384 rows at k = 16 30.6 / 13.9, 768 at 16
+// 25.2 / 19.2, 2256 at 64 136 / 70.5, 3756 at 64 189 / 148, the other way round 3072 at 16 66 / 76, 7500 at
+// 64 368 / 393, 2256 at 4 36 / 45; 64-token blocks 768 at 16 46 / 39, 1024 at 16 33.9 / 31.9, 1536 at 32 96 / 87,
+// 512 at 8 (fp32) 135 / 71, the other way round 2048 at 16 65 / 75, 3072 at 32 217 / 225.  In a sweep most values
+// of k find their scores in the cache: 1128 rows from k = 64 (blocks of 32) 110 / 95, from k = 32
+// (blocks of 64) 233 / 161, 2256 rows from 64 175 / 205.
+static bool few_rows(const Problem &pb, bool multi)
+{
+    const long long rows = (long long)pb.H * pb.NB;
+    if (multi) return rows <= (pb.b == 32 ? 20LL : 40LL) * pb.kmax;
+    return rows <= (pb.b == 32 ? 80LL : 64LL) * pb.kmax;
+}
+
 template <bool MULTI, bool BF16, int D, bool ARB>
-static level_fn pick_level_kernel_d(int bq, int bk, int kmax, int &wpr)
+static level_fn pick_level_kernel_d(int bq, int bk, int kmax, bool &split, int &wpr)
 {
     constexpr int OCC2 = (BF16 || D == 64) ? 2 : 1;
     constexpr bool BIG = BF16 || D == 64;           // 6 fragment groups + 8 accumulator tiles fit
     wpr = 1;
     const int mb = bq / 32, ng = bk / 32;
+    if (split) {
+        if (mb == 1 && ng == 1) return level_kernel<BF16, D, 1, 1, 1, 2, MULTI, ARB, 1, true>;
+        if constexpr (BF16 && !MULTI && !ARB)
+            if (mb == 2 && ng == 2 && kmax <= kShortListTopk) return level_kernel<BF16, D, 2, 1, 1, 2, MULTI, ARB, 2, true>;
+        if (mb == 2 && ng == 2) return level_kernel<BF16, D, 2, 2, 1, OCC2, MULTI, ARB, 1, true>;
+        split = false;
+    }
     if (mb == 4 && ng == 4) { wpr = 4; return level_kernel<BF16, D, 2, 2, 4, OCC2, MULTI, ARB>; }
     if (mb == 1 && ng == 1) return level_kernel<BF16, D, 1, 1, 1, 2, MULTI, ARB>;
     if constexpr (BF16 && !MULTI && !ARB)
@@ -502,20 +530,20 @@ static level_fn pick_level_kernel_d(int bq, int bk, int kmax, int &wpr)
 }
 
 template <bool MULTI, bool ARB>
-static level_fn pick_level_kernel_t(const Problem &pb, int &wpr)
+static level_fn pick_level_kernel_t(const Problem &pb, bool &split, int &wpr)
 {
     if (pb.dtype == STREAM_BF16)
-        return pb.d == 128 ? pick_level_kernel_d<MULTI, true, 128, ARB>(pb.b, pb.bk, pb.kmax, wpr)
-                           : pick_level_kernel_d<MULTI, true, 64, ARB>(pb.b, pb.bk, pb.kmax, wpr);
-    return pb.d == 128 ? pick_level_kernel_d<MULTI, false, 128, ARB>(pb.b, pb.bk, pb.kmax, wpr)
-                       : pick_level_kernel_d<MULTI, false, 64, ARB>(pb.b, pb.bk, pb.kmax, wpr);
+        return pb.d == 128 ? pick_level_kernel_d<MULTI, true, 128, ARB>(pb.b, pb.bk, pb.kmax, split, wpr)
+                           : pick_level_kernel_d<MULTI, true, 64, ARB>(pb.b, pb.bk, pb.kmax, split, wpr);
+    return pb.d == 128 ? pick_level_kernel_d<MULTI, false, 128, ARB>(pb.b, pb.bk, pb.kmax, split, wpr)
+                       : pick_level_kernel_d<MULTI, false, 64, ARB>(pb.b, pb.bk, pb.kmax, split, wpr);
 }
 
-static level_fn pick_level_kernel(const Problem &pb, bool multi, int &wpr)
+static level_fn pick_level_kernel(const Problem &pb, bool multi, bool &split, int &wpr)
 {
     if (pb.mask == STREAM_MASK_ARRAY)
-        return multi ? pick_level_kernel_t<true, true>(pb, wpr) : pick_level_kernel_t<false, true>(pb, wpr);
-    return multi ? pick_level_kernel_t<true, false>(pb, wpr) : pick_level_kernel_t<false, false>(pb, wpr);
+        return multi ? pick_level_kernel_t<true, true>(pb, split, wpr) : pick_level_kernel_t<false, true>(pb, split, wpr);
+    return multi ? pick_level_kernel_t<true, false>(pb, split, wpr) : pick_level_kernel_t<false, false>(pb, split, wpr);
 }
 
 }  // namespace stream
@@ -572,7 +600,8 @@ static stream_status run_prune(const void *Q, const void *K, const stream_shape 
     const bool wide = pb.kmax > kMaxTopk;       // more than one node per lane: the LDS-list kernel
     if (wide && !level_wide_supported(pb)) return STREAM_EUNSUPPORTED;
     int wpr = 1;
-    level_fn fn = wide ? nullptr : pick_level_kernel(pb, multi, wpr);
+    bool split = few_rows(pb, multi);
+    level_fn fn = wide ? nullptr : pick_level_kernel(pb, multi, split, wpr);
     if (!wide && !fn) return STREAM_EUNSUPPORTED;
     const PruneWorkspace w = prune_layout(pb);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return STREAM_EWORKSPACE;
@@ -631,7 +660,7 @@ static stream_status run_prune(const void *Q, const void *K, const stream_shape 
         return STREAM_OK;
     }
     const long long rows_per_kv = (long long)pb.NB * pb.g;
-    const long long per_kv = wpr == 1 ? (rows_per_kv + 3) / 4 : rows_per_kv;
+    const long long per_kv = wpr == 1 && !split ? (rows_per_kv + 3) / 4 : rows_per_kv;
     if (per_kv * pb.Hkv + 64 > 0x7fffffffLL) return STREAM_EUNSUPPORTED;
     p.map = make_wg_map(pb.Hkv, (int)per_kv);
     // levels per launch: every row runs that many of its levels back to back inside one kernel

@@ -27,8 +27,11 @@ __device__ __forceinline__ float key_to_score(unsigned u)
 // KH: a key block is scored in KH pieces of 32 * NG keys each (128 x 128 blocks: two pieces of 64
 // keys, the accumulators of a 128 x 128 tile do not fit one wavefront), the block's score being the
 // maximum over the pieces.
-template <bool BF16, int D, int MB, int NG, int KH, int OCC, bool ARB>
-__global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams p)
+// SPLIT: four wavefronts share a row, as in the narrow kernel's form of that name: wavefront w scores every
+// fourth listed block, the scores meet in wavefront 0's array, the bookkeeping is done by each on
+// lists of its own.
+template <bool BF16, int D, int MB, int NG, int KH, int OCC, bool ARB, bool SPLIT = false>
+__global__ void __launch_bounds__(SPLIT ? 256 : 128, OCC) level_wide_kernel(const PruneParams p)
 {
     constexpr int ES = BF16 ? 2 : 4;
     constexpr int FR = D * ES / 32;
@@ -49,7 +52,7 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
     int kvh, slot;
     if (!wg_decode(p.map, blockIdx.x, kvh, slot)) return;
     const long long rows_per_kv = (long long)p.NB * p.g;
-    const long long rk = (long long)slot * 2 + wave;
+    const long long rk = SPLIT ? (long long)slot : (long long)slot * 2 + wave;
     if (rk >= rows_per_kv) return;
     const int gb = p.NB - 1 - (int)(rk / p.g);            // long rows first
     const int h = kvh * p.g + (int)(rk % p.g);
@@ -89,7 +92,7 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
     int *nlb[2] = {base + 2 * KM, base + 3 * KM};
     float *nsb[2] = {(float *)(base + 4 * KM), (float *)(base + 5 * KM)};
     int *s_rep = base + 6 * KM;                           // [2 KM] blocks to score
-    float *s_sc = (float *)(base + 8 * KM);               // [2 KM] their scores
+    float *s_sc = (float *)((SPLIT ? smem : base) + 8 * KM);   // [2 KM] their scores (SPLIT: one array for the row)
     unsigned *s_key = (unsigned *)(base + 10 * KM);       // [2 KM] per branch position: source, then sort key
     int *s_brep = base + 12 * KM;                         // [2 KM] per branch position: representative
 
@@ -189,8 +192,9 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
 
         // ---- score the listed blocks (the narrow kernel's tile loop)
         uint4 kf[CG][KF];
-        if (nt > 0) {
-            const int r0 = __builtin_amdgcn_readfirstlane(s_rep[0]);
+        const int n_mine = SPLIT ? (nt - wave + 3) >> 2 : nt;     // this wavefront's blocks of the list
+        if (n_mine > 0) {
+            const int r0 = __builtin_amdgcn_readfirstlane(s_rep[SPLIT ? wave : 0]);
 #pragma unroll
             for (int fr = 0; fr < KF; ++fr)
 #pragma unroll
@@ -200,11 +204,11 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
                 }
         }
         float mx_block = -INFINITY;
-        for (int u = 0; u < nt * KH; ++u) {
-            const int t = u / KH, piece = u % KH;
+        for (int u = 0; u < n_mine * KH; ++u) {
+            const int t = SPLIT ? wave + 4 * (u / KH) : u / KH, piece = u % KH;
             const int r = __builtin_amdgcn_readfirstlane(s_rep[t]);
-            const int un = u + 1 < nt * KH ? u + 1 : u;
-            const unsigned nxt = (unsigned)__builtin_amdgcn_readfirstlane(s_rep[un / KH]) * (unsigned)TILE_BYTES;
+            const int un = u + 1 < n_mine * KH ? u + 1 : u;
+            const unsigned nxt = (unsigned)__builtin_amdgcn_readfirstlane(s_rep[SPLIT ? wave + 4 * (un / KH) : un / KH]) * (unsigned)TILE_BYTES;
             const int nxt_frag = (un % KH) * NG * FR;
             acc_t acc[RG][CG];
 #pragma unroll
@@ -287,6 +291,7 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
         }
         tiles_done += (unsigned long long)nt;
         wave_sync();
+        if constexpr (SPLIT) __syncthreads();             // the row's scores are complete
 
         // ---- per branch position: its score as an order-preserving integer key (0 = not a candidate)
         const int npos = 2 * cnt;
@@ -306,6 +311,7 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
             n_valid += __popcll(__ballot(key != 0));
         }
         wave_sync();
+        if constexpr (SPLIT) __syncthreads();             // ... and read by all, before the next level's are written
 
         // ---- the k-th largest key: threshold search over the bits, counts summed over the chunks
         unsigned thr = 1;            // n_valid <= k: every candidate is kept (keys are >= 1)
@@ -344,7 +350,8 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
         float *nso = nsb[nxt_buf];
         int out_base = 0, eq_seen = 0;
         const bool last = level == levels;
-        int *tr = p.trace ? p.trace + (((long long)(level - 1) * p.H * p.n_k * p.NB + row) * p.kmax) * 2 : nullptr;
+        const bool writer = !SPLIT || wave == 0;
+        int *tr = p.trace && writer ? p.trace + (((long long)(level - 1) * p.H * p.n_k * p.NB + row) * p.kmax) * 2 : nullptr;
         for (int c0 = 0; c0 < npos; c0 += 64) {
             const int pp = c0 + lane;
             const unsigned key = pp < npos ? s_key[pp] : 0u;
@@ -367,7 +374,7 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
                 const float s = key_to_score(key);
                 nfo[out] = cf; nlo[out] = cl; nso[out] = s;
                 if (tr) { tr[2 * out] = cf; tr[2 * out + 1] = cl; }
-                if (last) {
+                if (last && writer) {
                     p.idx[o + out] = s_brep[pp];
                     if (p.score) p.score[o + out] = s;
                 }
@@ -377,7 +384,7 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
         const int newcnt = out_base;
         if (tr)
             for (int j = newcnt + lane; j < p.kmax; j += 64) { tr[2 * j] = -1; tr[2 * j + 1] = -1; }
-        if (last) {
+        if (last && writer) {
             for (int j = newcnt + lane; j < p.kmax; j += 64) {
                 p.idx[o + j] = -1;
                 if (p.score) p.score[o + j] = -INFINITY;
@@ -387,7 +394,7 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
         wave_sync();
         cnt = newcnt;
         // rows that finish before the deepest one: their node list stays as it is
-        if (last && p.trace)
+        if (last && p.trace && writer)
             for (int lv = level + 1; lv <= p.max_levels; ++lv) {
                 int *t2 = p.trace + (((long long)(lv - 1) * p.H * p.n_k * p.NB + row) * p.kmax) * 2;
                 for (int j = lane; j < p.kmax; j += 64) {
@@ -397,17 +404,20 @@ __global__ void __launch_bounds__(128, OCC) level_wide_kernel(const PruneParams 
                 }
             }
     }
-    if (p.tiles && lane == 0) atomicAdd(p.tiles, tiles_done);
+    if (p.tiles && lane == 0 && (!SPLIT || wave == 0)) atomicAdd(p.tiles, tiles_done);
 }
 
 typedef void (*wide_fn)(const PruneParams);
 
 template <bool BF16, int D, bool ARB>
-static wide_fn pick_wide(int bq, int bk)
+static wide_fn pick_wide(int bq, int bk, bool &split)
 {
     constexpr int OCC2 = (BF16 || D == 64) ? 2 : 1;
     constexpr bool BIG = BF16 || D == 64;
     const int mb = bq / 32, ng = bk / 32;
+    if (split && mb == 1 && ng == 1) return level_wide_kernel<BF16, D, 1, 1, 1, 2, ARB, true>;
+    if (split && mb == 2 && ng == 2) return level_wide_kernel<BF16, D, 2, 2, 1, OCC2, ARB, true>;
+    split = false;
     if (mb == 1 && ng == 1) return level_wide_kernel<BF16, D, 1, 1, 1, 2, ARB>;
     if (mb == 2 && ng == 2) return level_wide_kernel<BF16, D, 2, 2, 1, OCC2, ARB>;
     if (mb == 1 && ng == 2) return level_wide_kernel<BF16, D, 1, 2, 1, OCC2, ARB>;
@@ -423,32 +433,43 @@ static wide_fn pick_wide(int bq, int bk)
 }
 
 template <bool ARB>
-static wide_fn pick_wide_mask(const Problem &pb)
+static wide_fn pick_wide_mask(const Problem &pb, bool &split)
 {
     return pb.dtype == STREAM_BF16
-               ? (pb.d == 128 ? pick_wide<true, 128, ARB>(pb.b, pb.bk) : pick_wide<true, 64, ARB>(pb.b, pb.bk))
-               : (pb.d == 128 ? pick_wide<false, 128, ARB>(pb.b, pb.bk) : pick_wide<false, 64, ARB>(pb.b, pb.bk));
+               ? (pb.d == 128 ? pick_wide<true, 128, ARB>(pb.b, pb.bk, split) : pick_wide<true, 64, ARB>(pb.b, pb.bk, split))
+               : (pb.d == 128 ? pick_wide<false, 128, ARB>(pb.b, pb.bk, split) : pick_wide<false, 64, ARB>(pb.b, pb.bk, split));
 }
 
-static wide_fn pick_wide_kernel(const Problem &pb)
+static wide_fn pick_wide_kernel(const Problem &pb, bool &split)
 {
     if (pb.kmax > kWideTopk) return nullptr;
-    return pb.mask == STREAM_MASK_ARRAY ? pick_wide_mask<true>(pb) : pick_wide_mask<false>(pb);
+    return pb.mask == STREAM_MASK_ARRAY ? pick_wide_mask<true>(pb, split) : pick_wide_mask<false>(pb, split);
 }
 
-bool level_wide_supported(const Problem &pb) { return pick_wide_kernel(pb) != nullptr; }
+bool level_wide_supported(const Problem &pb)
+{
+    bool split = false;
+    return pick_wide_kernel(pb, split) != nullptr;
+}
 
 stream_status launch_level_wide(const Problem &pb, const PruneParams &p_in, hipStream_t st)
 {
-    wide_fn fn = pick_wide_kernel(pb);
+    // Few rows: four wavefronts share one.  Four lists of nodes instead of two limit the workgroups a CU
+    // holds, so a shared row has to pay early.  us, own row / shared row (blocks of 32): 1692 rows at k = 65
+    // 122 / 64, 2628 at 80 171 / 106, 2628 at 200 190 / 105, the other way round 3840 at 70 181 / 187, 3840 at
+    // 256 196 / 234, 5628 at 100 332 / 351; blocks of 64: 3072 at 100 319 / 341.
+    const long long rows = (long long)pb.H * pb.NB;
+    bool split = rows <= (pb.b == 32 ? 3000 : 1500) && (size_t)4 * kWideWordsPerK * pb.kmax * 4 <= 65536;
+    wide_fn fn = pick_wide_kernel(pb, split);
     if (!fn) return STREAM_EUNSUPPORTED;
     PruneParams p = p_in;
     const long long rows_per_kv = (long long)pb.NB * pb.g;
-    const long long per_kv = (rows_per_kv + 1) / 2;                  // two rows (wavefronts) per workgroup
+    const long long per_kv = split ? rows_per_kv : (rows_per_kv + 1) / 2;   // a row, or two rows (wavefronts), per workgroup
     if (per_kv * pb.Hkv + 64 > 0x7fffffffLL) return STREAM_EUNSUPPORTED;
     p.map = make_wg_map(pb.Hkv, (int)per_kv);
-    const size_t lds = (size_t)2 * kWideWordsPerK * pb.kmax * 4;     // <= 57,344 bytes at k = 512
-    hipLaunchKernelGGL(fn, dim3((unsigned)p.map.grid), dim3(128), lds, st, p);
+    const int waves = split ? 4 : 2;
+    const size_t lds = (size_t)waves * kWideWordsPerK * pb.kmax * 4;        // two rows: <= 57,344 bytes at k = 512
+    hipLaunchKernelGGL(fn, dim3((unsigned)p.map.grid), dim3(64 * waves), lds, st, p);
     return hipGetLastError() == hipSuccess ? STREAM_OK : STREAM_EDEVICE;
 }
 
