@@ -12,6 +12,7 @@
 // key column, turns it into probabilities with the final row normalisers and adds the column
 // sums to mass[] with atomics.
 #include "stream_mfma.h"
+#include "stream_pack.h"
 
 #include <math.h>
 
@@ -19,27 +20,47 @@ namespace stream {
 
 
 // ---------------------------------------------------------------------------------------------
-// V packing.  Per 32-key group and per 32-feature block db, fragment vf holds for lane
+// Preparation, one launch: K and V packed and the received mass cleared, a workgroup per 32-key group of K
+// or V or per kZeroPerWg values.  Bound: memory, or the launch itself: 1 k tokens, 12/2 heads 4.3 us (a
+// launch each: 3.3 + 3.9 + 1.8, and two launches more for the host), 32 k tokens, 8 kv heads 43 us
+// (25 + 24), 131 k tokens 166 us = 6.6 TB/s (82 + 88 + 7).
+//
+// V: per 32-key group and per 32-feature block db, fragment vf holds for lane
 // (mrow = lane % 32, gh = lane / 32) the values V[key][db*32 + mrow] of the keys
 //     bf16: element e of fragment vf (2 per group): key = (2*vf + e/4)*8 + gh*4 + e%4
 //     fp32: element e of fragment vf (4 per group): key = vf*8 + gh*4 + e
 // which are exactly the key rows a lane's S^T accumulator elements cover, in order.
 // Layout: [kv_head][global block][group][db][vf][lane] x 16 bytes.
 // ---------------------------------------------------------------------------------------------
-struct PackVParams {
-    const char *src;
-    char *dst;
-    long long stride_h_bytes, stride_t_bytes;
+struct PrepParams {
+    const char *K, *V;
+    char *Kp, *Vp;
+    long long k_sh_b, k_st_b, v_sh_b, v_st_b;
     int d, esize, b, NB;
+    unsigned groups;             // 32-key groups of K (and of V)
+    float *mass;                 // nullable
+    long long mass_n;
     SeqTable seqs;
 };
 
-__global__ void __launch_bounds__(256) pack_v_kernel(PackVParams p)
+constexpr int kZeroPerWg = 2048;
+
+__global__ void __launch_bounds__(256) attn_prep_kernel(PrepParams p)
 {
+    const unsigned wg = blockIdx.x;
+    if (wg < p.groups) {
+        pack_group(p.K, p.Kp, p.k_sh_b, p.k_st_b, p.d * p.esize, p.b, p.NB, 0, p.seqs, wg);
+        return;
+    }
+    if (wg >= 2u * p.groups) {
+        const long long i0 = (long long)(wg - 2u * p.groups) * kZeroPerWg;
+        for (long long i = i0 + threadIdx.x; i < i0 + kZeroPerWg && i < p.mass_n; i += 256) p.mass[i] = 0.f;
+        return;
+    }
     const int groups = p.b / 32;
     const int ndb = p.d / 32;
     const int nvf = p.esize == 2 ? 2 : 4;
-    const long long grp = blockIdx.x;
+    const long long grp = wg - p.groups;
     const int gi = (int)(grp % groups);
     const long long t = grp / groups;
     const int gb = (int)(t % p.NB);
@@ -47,32 +68,37 @@ __global__ void __launch_bounds__(256) pack_v_kernel(PackVParams p)
     const int s = seq_of_block(p.seqs, gb);
     const SeqDesc sd = p.seqs.d[s];
     const int tok0 = (gb - sd.blk0) * p.b + gi * 32;
-    char *dst = p.dst + grp * (32LL * p.d * p.esize);
-    const char *src = p.src + kvh * p.stride_h_bytes;
+    char *dst = p.Vp + grp * (32LL * p.d * p.esize);
+    const char *src = p.V + kvh * p.v_sh_b;
     for (int c = threadIdx.x; c < ndb * nvf * 64; c += blockDim.x) {
         const int lane = c & 63, vf = (c >> 6) % nvf, db = (c >> 6) / nvf;
         const int mrow = lane & 31, gh = lane >> 5;
         uint4 out = make_uint4(0, 0, 0, 0);
+        // (tokens past the end of the sequence read its last one and are cleared afterwards: no branch
+        // around a load, all of them in flight together)
+        const char *col = src + sd.tok0 * p.v_st_b + (db * 32 + mrow) * p.esize;
+        const int last = sd.len - 1;
         if (p.esize == 2) {
-            unsigned short v[8];
+            unsigned v[8];
+#pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int key = (2 * vf + (e >> 2)) * 8 + gh * 4 + (e & 3);
-                const int tok = tok0 + key;
-                v[e] = tok < sd.len ? *reinterpret_cast<const unsigned short *>(
-                                          src + (sd.tok0 + tok) * p.stride_t_bytes + (db * 32 + mrow) * 2)
-                                    : (unsigned short)0;
+                const int tok = tok0 + (2 * vf + (e >> 2)) * 8 + gh * 4 + (e & 3);
+                v[e] = *reinterpret_cast<const unsigned short *>(col + (tok < last ? tok : last) * p.v_st_b);
             }
-            out.x = v[0] | ((unsigned)v[1] << 16); out.y = v[2] | ((unsigned)v[3] << 16);
-            out.z = v[4] | ((unsigned)v[5] << 16); out.w = v[6] | ((unsigned)v[7] << 16);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (tok0 + (2 * vf + (e >> 2)) * 8 + gh * 4 + (e & 3) > last) v[e] = 0u;
+            out = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
         } else {
             unsigned v[4];
+#pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int key = vf * 8 + gh * 4 + e;
-                const int tok = tok0 + key;
-                v[e] = tok < sd.len ? *reinterpret_cast<const unsigned *>(
-                                          src + (sd.tok0 + tok) * p.stride_t_bytes + (db * 32 + mrow) * 4)
-                                    : 0u;
+                const int tok = tok0 + vf * 8 + gh * 4 + e;
+                v[e] = *reinterpret_cast<const unsigned *>(col + (tok < last ? tok : last) * p.v_st_b);
             }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (tok0 + vf * 8 + gh * 4 + e > last) v[e] = 0u;
             out = make_uint4(v[0], v[1], v[2], v[3]);
         }
         *reinterpret_cast<uint4 *>(dst + (long long)c * 16) = out;
@@ -934,12 +960,6 @@ static AttnWorkspace attn_layout(const Problem &pb)
     return w;
 }
 
-__global__ void __launch_bounds__(256) zero_kernel(float *p, long long n)
-{
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.f;
-}
-
 }  // namespace stream
 
 using namespace stream;
@@ -986,24 +1006,21 @@ stream_status stream_sparse_attn(const void *Q, const void *K, const void *V,
     hipStream_t st = (hipStream_t)hip_stream;
     char *ws = (char *)workspace;
 
-    rc = launch_pack(K, k_sh, k_st, ws + w.kp, pb, st);
-    if (rc != STREAM_OK) return rc;
     {
-        PackVParams pv;
-        pv.src = (const char *)V;
-        pv.dst = ws + w.vp;
-        pv.stride_h_bytes = v_sh * pb.esize;
-        pv.stride_t_bytes = v_st * pb.esize;
-        pv.d = pb.d; pv.esize = pb.esize; pv.b = pb.b; pv.NB = pb.NB;
-        pv.seqs = pb.seqs;
-        const long long grid = (long long)pb.Hkv * pb.NB * (pb.b / 32);
+        PrepParams pp;
+        pp.K = (const char *)K; pp.V = (const char *)V;
+        pp.Kp = ws + w.kp; pp.Vp = ws + w.vp;
+        pp.k_sh_b = k_sh * pb.esize; pp.k_st_b = k_st * pb.esize;
+        pp.v_sh_b = v_sh * pb.esize; pp.v_st_b = v_st * pb.esize;
+        pp.d = pb.d; pp.esize = pb.esize; pp.b = pb.b; pp.NB = pb.NB;
+        pp.seqs = pb.seqs;
+        pp.mass = mass;
+        pp.mass_n = mass ? (long long)pb.H * pb.T : 0;
+        const long long groups = (long long)pb.Hkv * pb.NB * (pb.b / 32);
+        const long long grid = 2 * groups + (pp.mass_n + kZeroPerWg - 1) / kZeroPerWg;
         if (grid > 0x7fffffffLL) return STREAM_EUNSUPPORTED;
-        hipLaunchKernelGGL(pack_v_kernel, dim3((unsigned)grid), dim3(256), 0, st, pv);
-        if (hipGetLastError() != hipSuccess) return STREAM_EDEVICE;
-    }
-    if (mass) {
-        const long long n = (long long)pb.H * pb.T;
-        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, mass, n);
+        pp.groups = (unsigned)groups;
+        hipLaunchKernelGGL(attn_prep_kernel, dim3((unsigned)grid), dim3(256), 0, st, pp);
         if (hipGetLastError() != hipSuccess) return STREAM_EDEVICE;
     }
     AttnParams p;

@@ -1,5 +1,5 @@
 // Host-side argument validation shared by the entry points, and the K/V tile packer.
-#include "stream_common.h"
+#include "stream_pack.h"
 
 namespace stream {
 
@@ -88,26 +88,7 @@ stream_status make_problem(const stream_shape *s, int topk, const int *topk_per_
     return STREAM_OK;
 }
 
-// ---------------------------------------------------------------------------------------------
-// Tile packing.
-//
-// A 32x32 MFMA reads, per lane, 16 contiguous bytes of one operand row: lane (n = lane % 32,
-// g = lane / 32) supplies row n, and the g-th half of the fragment's slice of the contraction
-// axis.  Reading those 16 bytes straight from a row-major [token, d] tensor makes every lane of
-// a load instruction touch a different row.  The packer therefore rewrites each group of 32
-// tokens so that the 64 lanes' chunks of fragment `fr` are contiguous (1 KiB per fragment):
-//
-//     dst chunk (fr * 64 + g * 32 + n)  <-  src row n, 16-byte chunk (2 * fr + g)
-//
-// A block of b tokens is b/32 consecutive groups; tokens past the end of a sequence are zero
-// (they are masked out wherever they could matter).  Layout: [kv_head][global block][b * d].
-// The permutation is per 32-token group, so the same packed tensor serves every block size.
-// With kPackFrag16 (operands of the 16x16x32 bf16 MFMA: lane (g = lane / 16, n = lane % 16) supplies
-// row n and the g-th 16-byte chunk of the fragment's 64-byte slice) the group is cut into
-// fragments of 16 rows x 64 bytes instead:
-//
-//     dst chunk ((n / 16 * (row_bytes / 64) + cc / 4) * 64 + (cc % 4) * 16 + n % 16)  <-  src row n, chunk cc
-// ---------------------------------------------------------------------------------------------
+// K packed by itself: see pack_group.
 struct PackParams {
     const char *src;
     char *dst;
@@ -120,34 +101,7 @@ struct PackParams {
 
 __global__ void __launch_bounds__(256) pack_kernel(PackParams p)
 {
-    const int cpr = p.row_bytes / 16;         // 16-byte chunks per row
-    const int groups = p.b / 32;
-    const long long grp = blockIdx.x;          // (kvh * NB + gb) * groups + gi
-    const int gi = (int)(grp % groups);
-    const long long t = grp / groups;
-    const int gb = (int)(t % p.NB);
-    const int kvh = (int)(t / p.NB);
-    const int s = seq_of_block(p.seqs, gb);
-    const SeqDesc sd = p.seqs.d[s];
-    const int r = gb - sd.blk0;
-    const int tok_in_seq0 = r * p.b + gi * 32;
-    char *dst = p.dst + grp * (32LL * p.row_bytes);
-    for (int c = threadIdx.x; c < 32 * cpr; c += blockDim.x) {
-        const int n = c / cpr, cc = c % cpr;
-        const int fr = cc >> 1, g = cc & 1;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        const int tok = tok_in_seq0 + n;
-        if (tok < sd.len)
-            v = *reinterpret_cast<const uint4 *>(p.src + kvh * p.stride_h_bytes +
-                                                 (sd.tok0 + tok) * p.stride_t_bytes + cc * 16);
-        int chunk = fr * 64 + g * 32 + n;
-        if (p.frag16) {
-            // fragment (16-row group n / 16, 64-byte slice cc / 4), lane (chunk cc % 4 of the slice, row n % 16)
-            const int kf = cpr >> 2;
-            chunk = ((n >> 4) * kf + (cc >> 2)) * 64 + (cc & 3) * 16 + (n & 15);
-        }
-        *reinterpret_cast<uint4 *>(dst + chunk * 16) = v;
-    }
+    pack_group(p.src, p.dst, p.stride_h_bytes, p.stride_t_bytes, p.row_bytes, p.b, p.NB, p.frag16, p.seqs, blockIdx.x);
 }
 
 stream_status launch_pack(const void *src, long long stride_h, long long stride_t, void *dst,
