@@ -191,8 +191,8 @@ def stream_prune(Q: torch.Tensor, K: torch.Tensor, heads: int, kv_heads: int, bl
         score = torch.empty((H, NB, kmax), dtype=torch.float32, device=dev) if want_score else None
     else:
         idx, cnt, score = out["idx"], out["cnt"], out.get("score")
-    need = lib.stream_prune_workspace_bytes(ctypes.byref(shape), kmax)
     if workspace is None:
+        need = lib.stream_prune_workspace_bytes(ctypes.byref(shape), kmax)
         workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=dev)
     diag = StreamPruneDiag()
     trace = tiles = None
@@ -277,8 +277,8 @@ def stream_prune_multi(Q: torch.Tensor, K: torch.Tensor, heads: int, kv_heads: i
         score = torch.empty((H, n_k, NB, kmax), dtype=torch.float32, device=dev) if want_score else None
     else:
         idx, cnt, score = out["idx"], out["cnt"], out.get("score")
-    need = lib.stream_prune_multi_workspace_bytes(ctypes.byref(shape), n_k, kmax)
     if workspace is None:
+        need = lib.stream_prune_multi_workspace_bytes(ctypes.byref(shape), n_k, kmax)
         workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=dev)
     diag = StreamPruneDiag()
     tiles = None
@@ -318,8 +318,8 @@ def stream_prune_variable(Q: torch.Tensor, K: torch.Tensor, heads: int, kv_heads
         score = torch.empty((H, NB, kmax), dtype=torch.float32, device=dev) if want_score else None
     else:
         idx, cnt, score = out["idx"], out["cnt"], out.get("score")
-    need = lib.stream_prune_workspace_bytes(ctypes.byref(shape), kmax)
     if workspace is None:
+        need = lib.stream_prune_workspace_bytes(ctypes.byref(shape), kmax)
         workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=dev)
     diag = StreamPruneDiag()
     trace = tiles = None
@@ -359,8 +359,8 @@ def stream_sparse_attn(Q, K, V, heads: int, kv_heads: int, block: int, idx, cnt,
         raise ValueError("idx/cnt must be contiguous int32 device tensors")
     lse = (torch.empty((H, T), dtype=torch.float32, device=dev) if out is None else out.get("lse")) if want_lse else None
     mass = (torch.empty((H, T), dtype=torch.float32, device=dev) if out is None else out.get("mass")) if want_mass else None
-    need = lib.stream_sparse_attn_workspace_bytes(ctypes.byref(shape), kmax)
     if workspace is None:
+        need = lib.stream_sparse_attn_workspace_bytes(ctypes.byref(shape), kmax)
         workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=dev)
     rc = lib.stream_sparse_attn(Q.data_ptr(), K.data_ptr(), V.data_ptr(), ctypes.byref(shape),
                                 idx.data_ptr(), cnt.data_ptr(), kmax, float(scale), O.data_ptr(),
@@ -457,8 +457,8 @@ def stream_receiver_stats(Q, K, heads: int, kv_heads: int, block: int, scale: fl
         hs = torch.empty((H, batch, 2), dtype=torch.float32, device=dev)
     else:
         bm, cm, ck, hs = out.get("block_mean"), out["col_mean"], out["col_kurt"], out["head"]
-    need = lib.stream_receiver_stats_workspace_bytes(ctypes.byref(shape))
     if workspace is None:
+        need = lib.stream_receiver_stats_workspace_bytes(ctypes.byref(shape))
         workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=dev)
     rc = lib.stream_receiver_stats(Q.data_ptr(), K.data_ptr(), ctypes.byref(shape), float(scale),
                                    bm.data_ptr() if bm is not None else None, cm.data_ptr(),
