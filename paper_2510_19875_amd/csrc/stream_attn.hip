@@ -200,18 +200,20 @@ struct AttnRow {
         ts = (ts < n_tiles ? ts : n_tiles - 1) + rot;
         return ts < n_tiles ? ts : ts - n_tiles;
     }
-    // The list entry of the t-th sub-tile as the list holds it.  A long list sits in LDS: the loops fetch
-    // an entry two sub-tiles ahead of its use, so that the read is not waited for.
+    // A long list sits in LDS: the loops fetch the entry of a sub-tile two sub-tiles ahead of its use, so that
+    // the read is not waited for.  (A list in a register is read where it is needed: fetched ahead like this
+    // it cost pass 2 2.71 instead of 2.41 ms at 131 k tokens.)
     __device__ __forceinline__ int fetch(int t) const
     {
         if constexpr (WIDE) return blk[place(t) >> ksh];
-        else return __builtin_amdgcn_readlane(my_blk, place(t) >> ksh);
+        else return 0;
     }
-    // 32-key group of the sequence that the t-th sub-tile covers, `raw` being its entry (fetched before)
+    // 32-key group of the sequence that the t-th sub-tile covers, `raw` being its entry (WIDE: fetched before)
     __device__ __forceinline__ int group(int t, int raw) const
     {
-        const int e = WIDE ? __builtin_amdgcn_readfirstlane(raw) & 0x7fffffff : raw;
-        return (e << ksh) + (place(t) & ((1 << ksh) - 1));
+        const int ts = place(t);
+        const int e = WIDE ? __builtin_amdgcn_readfirstlane(raw) & 0x7fffffff : __builtin_amdgcn_readlane(my_blk, ts >> ksh);
+        return (e << ksh) + (ts & ((1 << ksh) - 1));
     }
     // does the mask C (or the end of the sequence) cut through sub-tile t, which starts at key k0?
     __device__ __forceinline__ bool masked(int t, int k0, int raw) const
@@ -336,7 +338,7 @@ __device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, unsigned i
     // around: a full sweep takes as long as R rows take to be started, so all rows in flight pass the
     // same keys at the same time.  (The order of the sub-tiles does not matter to the result, and
     // it depends on the row alone, so runs are reproducible.)  131 k tokens, 32/8 heads, k = 32: requests
-    // of pass 1 that miss the L2 55 % -> 38 %, pass 1 5.40 -> 4.71 ms, pass 2 2.54 -> 2.44 ms; with half or
+    // of pass 1 that miss the L2 55 % -> 38 %, pass 1 5.40 -> 4.71 ms, pass 2 2.54 -> 2.41 ms; with half or
     // twice the true R 5.72 and 5.08 ms; where a list has a handful of blocks or the keys fit the L2, no change.
     r.rot = 0;
     if constexpr (!SPLIT) {
