@@ -1,7 +1,8 @@
 // stream_sparse_attn: Eq. (2) of the paper on the retained key blocks, gfx950.
 //
 // A wavefront owns up to 64 query tokens of one (head, query block) and walks the block's
-// retained key blocks in ascending order with a running softmax.  K tiles come from the same
+// retained key blocks in list order, from a place of its own on and around the end; where rows are few
+// the four wavefronts of a workgroup share a row.  K tiles come from the same
 // packed layout the pruning kernels use; V tiles are packed transposed so that a lane's 16
 // bytes hold one feature of the 8 (bf16) or 4 (fp32) keys its MFMA contraction slots cover.
 //
@@ -17,7 +18,6 @@
 #include <math.h>
 
 namespace stream {
-
 
 // ---------------------------------------------------------------------------------------------
 // Preparation, one launch: K and V packed and the received mass cleared, a workgroup per 32-key group of K
