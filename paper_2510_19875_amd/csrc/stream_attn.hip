@@ -635,8 +635,15 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
         safe = true;
     }
 
+    int l_exp[NQ];                                // the sum is l_tot * 2^l_exp (0 unless merged)
+#pragma unroll
+    for (int cq = 0; cq < NQ; ++cq) l_exp[cq] = 0;
     if constexpr (SPLIT) {
-        // the wavefronts' references, sums and outputs: one reference per query, everything scaled to it
+        // the wavefronts' references, sums and outputs: one reference per query, everything scaled to it.
+        // A sum may lie anywhere from 1 to 3e38 times 2^reference, so a wavefront's weight is its reference
+        // plus the exponent of its sum: the largest of those is what the others are scaled to, and the sums
+        // enter with their exponent taken out.  (Scaled by the references alone, a sum of 2^127 whose
+        // reference lies 127 octaves below another's would be lost, and sums of 2^127 each would overflow.)
         if (gh == 0) {
 #pragma unroll
             for (int cq = 0; cq < NQ; ++cq) {
@@ -647,22 +654,32 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
         }
         __syncthreads();                          // (also: every wavefront is done with its Q fragments)
         float own[NQ];
+        int own_exp[NQ];
 #pragma unroll
         for (int cq = 0; cq < NQ; ++cq) {
             const int qi = cq * 32 + col;
-            float m = -INFINITY;
+            float m = -INFINITY, top = -INFINITY;
+            int e = 0;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) m = fmaxf(m, s_ml[w][0][qi]);
+            for (int w = 0; w < 4; ++w) {
+                const float mw = s_ml[w][0][qi];
+                const int ew = __builtin_amdgcn_frexp_expf(s_ml[w][1][qi]);
+                const float key = mw + (float)ew;
+                if (key > top) { top = key; m = mw; e = ew; }
+            }
             const float m_use = m == -INFINITY ? 0.f : m;
-            own[cq] = __builtin_amdgcn_exp2f(m_run[cq] - m_use);
+            own_exp[cq] = __builtin_amdgcn_frexp_expf(l_tot[cq]);
+            own[cq] = __builtin_amdgcn_exp2f((m_run[cq] - m_use) + (float)(own_exp[cq] - e));
             float l = 0.f, lr = 0.f;
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                const float f = __builtin_amdgcn_exp2f(s_ml[w][0][qi] - m_use);
-                l += s_ml[w][1][qi] * f;
-                lr += s_ml[w][2][qi] * f;
+                const float lw = s_ml[w][1][qi];
+                const int ew = __builtin_amdgcn_frexp_expf(lw);
+                const float f = __builtin_amdgcn_exp2f((s_ml[w][0][qi] - m_use) + (float)(ew - e));
+                l += __builtin_amdgcn_ldexpf(lw, -ew) * f;
+                lr += __builtin_amdgcn_ldexpf(s_ml[w][2][qi], -ew) * f;
             }
-            m_run[cq] = m; l_tot[cq] = l; lr_tot[cq] = lr;
+            m_run[cq] = m; l_tot[cq] = l; l_exp[cq] = e;
             own[cq] *= lr > 0.f ? 1.f / lr : 0.f;
         }
         constexpr int LPR = 8, FPL = O_URB / 4 / LPR;          // lanes per row, features per lane
@@ -677,8 +694,10 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
                     for (int i4 = 0; i4 < 4; ++i4) {
                         const int db = u * O_NDBU + dbu;
                         float4 v;
-                        v.x = acc_o[db][cq][i4 * 4 + 0] * own[cq]; v.y = acc_o[db][cq][i4 * 4 + 1] * own[cq];
-                        v.z = acc_o[db][cq][i4 * 4 + 2] * own[cq]; v.w = acc_o[db][cq][i4 * 4 + 3] * own[cq];
+                        v.x = __builtin_amdgcn_ldexpf(acc_o[db][cq][i4 * 4 + 0], -own_exp[cq]) * own[cq];
+                        v.y = __builtin_amdgcn_ldexpf(acc_o[db][cq][i4 * 4 + 1], -own_exp[cq]) * own[cq];
+                        v.z = __builtin_amdgcn_ldexpf(acc_o[db][cq][i4 * 4 + 2], -own_exp[cq]) * own[cq];
+                        v.w = __builtin_amdgcn_ldexpf(acc_o[db][cq][i4 * 4 + 3], -own_exp[cq]) * own[cq];
                         *reinterpret_cast<float4 *>(my_lds + col * O_URS + (dbu * 32 + i4 * 8 + gh * 4) * 4) = v;
                     }
                 __syncthreads();
@@ -760,7 +779,7 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
 #pragma unroll
     for (int cq = 0; cq < NQ; ++cq) {
         const int tok = qtok0 + cq * 32 + col;
-        const float lse2 = l_tot[cq] > 0.f ? m_run[cq] + log2f(l_tot[cq]) : -INFINITY;
+        const float lse2 = l_tot[cq] > 0.f ? m_run[cq] + (log2f(l_tot[cq]) + (float)l_exp[cq]) : -INFINITY;
         if (tok < L && gh == 0) {
             if (p.lse) p.lse[(long long)r.h * p.T + r.tok0 + tok] = lse2 * 0.6931471805599453f;
             if (p.lse2) p.lse2[(long long)r.h * p.T + r.tok0 + tok] = lse2;

@@ -72,3 +72,51 @@ def test_shared_rows_match_whole_rows_and_the_oracle(T, block, k, dtype, d, mask
         seen = ~np.isneginf(ref["lse"][0])
         assert np.abs(lse[:, seen] - ref["lse"][:, seen]).max() <= 1e-3
         assert (np.abs(mass - ref["mass"]) / np.maximum(ref["mass"], 1.0)).max() <= 1e-3
+
+
+def steep(block, dtype, d, n_sub):
+    """Heads whose scores lie near 0 but for two keys 110 to 140 octaves up, in 32-key sub-tiles of one
+    wavefront's share or of two, ahead of or after sub-tiles without any."""
+    octaves = (110.0, 118.0, 125.5, 126.5, 127.0, 127.625, 129.0, 140.0)
+    places = ((1, 4), (4, 5), (4, 8), (5, 11))
+    H, T = len(octaves) * len(places), 32 * n_sub - 27
+    g = torch.Generator().manual_seed(3)
+    Q, K, V = (torch.randn((H, T, d), generator=g) * s for s in (0.3, 0.3, 1.0))
+    Q[:, :, :2] = 1.0
+    K[:, :, :2] = 0.0
+    for h in range(H):
+        x, place = octaves[h % len(octaves)], places[h // len(octaves)]
+        for i, sub in enumerate(place):
+            key = 32 * sub + 3 + i
+            K[h, key, 2:] = 0.0
+            K[h, key, 0], K[h, key, 1] = int(x), x - int(x)
+    ty = torch.bfloat16 if dtype == "bf16" else torch.float32
+    return H, T, Q.to(ty), K.to(ty), V.to(ty)
+
+
+@pytest.mark.parametrize("block,dtype,d,n_sub", [(32, "bf16", 128, 13), (64, "bf16", 128, 14), (128, "bf16", 64, 16),
+                                                 (32, "f32", 64, 13), (64, "f32", 128, 14), (32, "bf16", 64, 66)])
+def test_steep_scores(block, dtype, d, n_sub):
+    """Sums up to 2^128 times their reference, on references up to 140 octaves apart: the weights of two keys
+    that far above the rest are a half each, wherever they lie in a row and whichever form runs it."""
+    H, T, Q, K, V = steep(block, dtype, d, n_sub)
+    N = -(-T // block)
+    idx = np.full((H, N, N), -1, np.int32)
+    for q in range(N):
+        idx[:, q, :q + 1] = np.arange(q + 1)
+    cnt = np.broadcast_to(np.arange(1, N + 1, dtype=np.int32), (H, N)).copy()
+    scale = math.log(2.0)
+    ref = so.sparse_attn(Q.float().numpy(), K.float().numpy(), V.float().numpy(), H, H, block, idx, cnt, scale)
+    rows, sub_tiles = H * N * (2 if block == 128 else 1), N * (block // 32)
+    assert rows <= min(3000, 60 * sub_tiles)
+    for n in (1, 60 * sub_tiles // rows + 1):
+        print(f"[steep] b={block} {dtype} d={d} T={T} heads={H * n}", flush=True)
+        rep = lambda x: x.to(DEV).repeat(n, 1, 1)
+        a = binding.stream_sparse_attn(rep(Q), rep(K), rep(V), H * n, H * n, block, rep(torch.from_numpy(idx)),
+                                       torch.from_numpy(cnt).to(DEV).repeat(n, 1), scale, want_lse=True, want_mass=True)
+        torch.cuda.synchronize()
+        for c in range(n):
+            O, lse, mass = (a[x][c * H:(c + 1) * H].float().cpu().numpy() for x in ("O", "lse", "mass"))
+            assert np.abs(O - ref["O"]).max() <= TOL[dtype]
+            assert np.abs(lse - ref["lse"]).max() <= 1e-3
+            assert (np.abs(mass - ref["mass"]) / np.maximum(ref["mass"], 1.0)).max() <= 1e-3
