@@ -62,7 +62,10 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
     __shared__ float s_ns[4][kMaxTopk];
     // k sweep: block scores this row has computed so far, whatever k they were computed for
     // (entry = block id << 32 | score bits, direct mapped; a miss only costs a recomputation)
-    __shared__ unsigned long long s_cache[MULTI ? 4 : 1][MULTI ? kScoreCache : 1];
+    // SPLIT: one cache for the row, written by wavefront 0 and read by all four.  (Where two blocks of one
+    // level fall on the same entry it is not defined which stays: caches of their own could come to
+    // differ, and the wavefronts with them in the list of blocks that they score together.)
+    __shared__ unsigned long long s_cache[MULTI && !SPLIT ? 4 : 1][MULTI ? kScoreCache : 1];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keep it scalar
@@ -121,9 +124,11 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
         __builtin_amdgcn_sched_barrier(0);
     }
 
+    const int cache = SPLIT ? 0 : wave;
     if constexpr (MULTI) {
-        for (int i = lane; i < kScoreCache; i += 64) s_cache[wave][i] = ~0ull;
-        wave_sync();
+        for (int i = SPLIT ? (int)threadIdx.x : lane; i < kScoreCache; i += SPLIT ? 256 : 64) s_cache[cache][i] = ~0ull;
+        if constexpr (SPLIT) __syncthreads();
+        else wave_sync();
     }
     unsigned long long tiles_done = 0;
     const int n_k = MULTI ? p.n_k : 1;
@@ -226,12 +231,12 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
         if constexpr (MULTI) {
             // a score of the same block computed earlier for this row (another k, another level)
             if (need0) {
-                const unsigned long long e = s_cache[wave][rep0 & (kScoreCache - 1)];
+                const unsigned long long e = s_cache[cache][rep0 & (kScoreCache - 1)];
                 hit0 = (int)(e >> 32) == rep0;
                 c0 = __builtin_bit_cast(float, (unsigned)e);
             }
             if (need1) {
-                const unsigned long long e = s_cache[wave][rep1 & (kScoreCache - 1)];
+                const unsigned long long e = s_cache[cache][rep1 & (kScoreCache - 1)];
                 hit1 = (int)(e >> 32) == rep1;
                 c1 = __builtin_bit_cast(float, (unsigned)e);
             }
@@ -372,9 +377,11 @@ __global__ void __launch_bounds__(256, OCC) level_kernel(const PruneParams p)
         float s0 = -INFINITY, s1 = -INFINITY;
         if (v0) s0 = need0 ? tile_score(pos0) : (hit0 ? c0 : sc);
         if (v1) s1 = need1 ? tile_score(pos1) : (hit1 ? c1 : sc);
-        if constexpr (MULTI) {
-            if (need0) s_cache[wave][rep0 & (kScoreCache - 1)] = ((unsigned long long)(unsigned)rep0 << 32) | __builtin_bit_cast(unsigned, s0);
-            if (need1) s_cache[wave][rep1 & (kScoreCache - 1)] = ((unsigned long long)(unsigned)rep1 << 32) | __builtin_bit_cast(unsigned, s1);
+        // (SPLIT: all four have looked this level up before the barrier above, and look the next one up
+        // after the barrier below)
+        if (MULTI && (!SPLIT || wave == 0)) {
+            if (need0) s_cache[cache][rep0 & (kScoreCache - 1)] = ((unsigned long long)(unsigned)rep0 << 32) | __builtin_bit_cast(unsigned, s0);
+            if (need1) s_cache[cache][rep1 & (kScoreCache - 1)] = ((unsigned long long)(unsigned)rep1 << 32) | __builtin_bit_cast(unsigned, s1);
         }
         // the four wavefronts of a row must all have read this level's tile scores before any of
         // them writes the next level's

@@ -86,3 +86,20 @@ def test_sweep_and_variable_k(T, block, ks, mask):
         single = binding.stream_prune(Q.to(DEV), K.to(DEV), 1, 1, block, k, want_score=True, **gpu)
         assert torch.equal(one["idx"][0, i, :, :k], single["idx"][0])
         assert torch.equal(one["score"][0, i, :, :k], single["score"][0])
+
+
+@pytest.mark.parametrize("block,T", [(32, 32 * 1100 - 9), (64, 64 * 2100 - 30)])
+def test_sweep_over_more_blocks_than_the_score_cache_holds(block, T):
+    """Blocks of one level that fall on the same entry of the row's score cache (1024 entries)."""
+    ks = (64, 32, 7, 1)
+    g = torch.Generator().manual_seed(9)
+    Q, K = (torch.randn((1, T, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(2))
+    assert 1024 < -(-T // block) <= (20 if block == 32 else 40) * max(ks)
+    print(f"[split] sweep T={T} b={block}", flush=True)
+    multi = binding.stream_prune_multi(Q, K, 1, 1, block, list(ks), want_score=True)
+    for i, k in enumerate(ks):
+        one = binding.stream_prune(Q, K, 1, 1, block, k, want_score=True)
+        torch.cuda.synchronize()
+        assert torch.equal(multi["cnt"][0, i], one["cnt"][0])
+        assert torch.equal(multi["idx"][0, i, :, :k], one["idx"][0])
+        assert torch.equal(multi["score"][0, i, :, :k], one["score"][0])
