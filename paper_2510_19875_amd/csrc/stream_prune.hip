@@ -520,9 +520,7 @@ static level_fn pick_level_kernel_d(int bq, int bk, int kmax, bool &split, int &
         split = false;
     }
     if (mb == 4 && ng == 4) { wpr = 4; return level_kernel<BF16, D, 2, 2, 4, OCC2, MULTI, ARB>; }
-    // (the sweep's kernel needs 7 registers more than leave room for a fourth wavefront on a SIMD; held to
-    // that it spills 6 and is faster: 20 k tokens, 12/2 heads, seven values of k 548 -> 534 us)
-    if (mb == 1 && ng == 1) return level_kernel<BF16, D, 1, 1, 1, (BF16 && D == 128 && MULTI && !ARB) ? 4 : 2, MULTI, ARB>;
+    if (mb == 1 && ng == 1) return level_kernel<BF16, D, 1, 1, 1, 2, MULTI, ARB>;
     if constexpr (BF16 && !MULTI && !ARB)
         if (mb == 2 && ng == 2 && kmax <= kShortListTopk) return level_kernel<BF16, D, 2, 1, 1, 2, MULTI, ARB, 2>;
     if (mb == 2 && ng == 2) return level_kernel<BF16, D, 2, 2, 1, OCC2, MULTI, ARB>;
