@@ -188,7 +188,7 @@ struct AttnRow {
     int my_blk;                                 // lane j holds list entry j (not WIDE)
     int *blk;                                   // this wavefront's list in LDS (WIDE)
     int n_tiles;                                // 32-key sub-tiles of the row's list that can hold a visible key
-    int rot;                                    // where in the list the row starts (sub-tiles); it wraps around at the end
+    int rot;                                    // sub-tiles by which the walk behind the list's first one is shifted (< n_tiles)
     bool plain_list;                            // not what stream_prune writes: every sub-tile is masked token by token
     unsigned long long allmask;                 // ARB: bit j = list entry j is wholly visible to the query block
 
@@ -196,9 +196,11 @@ struct AttnRow {
     __device__ __forceinline__ int place(int t) const
     {
         int ts = __builtin_amdgcn_readfirstlane(t);
-        if constexpr (SPLIT) return ts < n_tiles ? ts : n_tiles - 1;
-        ts = (ts < n_tiles ? ts : n_tiles - 1) + rot;
-        return ts < n_tiles ? ts : ts - n_tiles;
+        ts = ts < n_tiles ? ts : n_tiles - 1;
+        if constexpr (SPLIT) return ts;
+        // the head of the list first, then from `rot` on and around the end
+        const int tr = ts + rot;
+        return ts == 0 ? 0 : (tr < n_tiles ? tr : tr - (n_tiles - 1));
     }
     // A long list sits in LDS: the loops fetch the entry of a sub-tile two sub-tiles ahead of its use, so that
     // the read is not waited for.  (A list in a register is read where it is needed: fetched ahead like this
@@ -334,16 +336,21 @@ __device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, unsigned i
     // An XCD works on the keys of one kv head at a time, far more than its L2 holds, and what a row
     // finds there is what other rows in flight have just read.  Rows start one after the other, so if each
     // began at the head of its list they would be spread over the whole key axis at any moment.
-    // Instead row i of the R an XCD has in flight starts i/R of the way through its list and wraps
-    // around: a full sweep takes as long as R rows take to be started, so all rows in flight pass the
-    // same keys at the same time.  (The order of the sub-tiles does not matter to the result, and
-    // it depends on the row alone, so runs are reproducible.)  131 k tokens, 32/8 heads, k = 32: requests
+    // Instead row i of the R an XCD has in flight goes, after the first sub-tile, to i/R of the way through
+    // its list and wraps around: a full sweep takes as long as R rows take to be started, so all rows in
+    // flight pass the same keys at the same time.  The first sub-tile of the list stays the first one visited:
+    // it usually holds the heaviest key (the sink), whose probability is then 1 before it is rounded to
+    // bf16.  (From i/R on without it: error of O against 64 bits 1.85e-3 instead of 1.81e-3 at 10 k tokens, of the
+    // mass 4.1e-7 instead of 3.1e-7; time the same.)  The order of the sums depends on the row's place in
+    // the launch: O and lse repeat from call to call, not from one number of heads or packing to another.
+    // The mass is added up with atomics, in no fixed order.  131 k tokens, 32/8 heads, k = 32: requests
     // of pass 1 that miss the L2 55 % -> 38 %, pass 1 5.40 -> 4.71 ms, pass 2 2.54 -> 2.41 ms; with half or
     // twice the true R 5.72 and 5.08 ms; where a list has a handful of blocks or the keys fit the L2, no change.
     r.rot = 0;
     if constexpr (!SPLIT) {
         const unsigned phase = (blockIdx.x / kXcds) % in_flight;
-        r.rot = __builtin_amdgcn_readfirstlane((int)(((unsigned)n_blk * phase / in_flight) << r.ksh));
+        const int rot = (int)(((unsigned)n_blk * phase / in_flight) << r.ksh);
+        r.rot = __builtin_amdgcn_readfirstlane(rot < n_tiles ? rot : (n_tiles > 0 ? n_tiles - 1 : 0));
     }
     // ARB: one lane per entry looks its block up once, the loops then test a scalar bit per sub-tile
     r.allmask = 0;

@@ -98,11 +98,11 @@ def test_full_mask_equals_torch_causal_attention_on_gpu():
 
 @pytest.mark.parametrize("kind", ["overflow", "vanish"])
 def test_fixed_reference_falls_back_to_the_tracked_order(kind):
-    """The pipelined loop keeps the softmax reference of the sub-tile before it.  Scores that
-    then jump by hundreds of octaves (overflow), or a row whose first visible keys sit hundreds
-    of octaves above everything else seen later under a zero reference (vanish), must come out
-    right: the kernel notices the non-finite / vanished sums and recomputes the row while
-    tracking the maximum."""
+    """A row keeps the softmax reference of the first sub-tile in which every query sees a key.  Scores that
+    then jump by hundreds of octaves (overflow), or a row whose first keys sit hundreds of octaves above
+    everything seen later, under a sliding window that hides them from most queries (vanish), must come
+    out right: the kernel notices the non-finite / vanished sums and recomputes the row while tracking the
+    maximum.  (These few rows are shared ones; test_steep_scores has both forms.)"""
     dev = torch.device("cuda:0")
     H, T, d, b = 2, 64 * 8 + 5, 128, 64
     g = torch.Generator().manual_seed(5)
@@ -131,6 +131,44 @@ def test_fixed_reference_falls_back_to_the_tracked_order(kind):
     np.testing.assert_allclose(out["lse"].cpu().numpy(), ref["lse"], rtol=1e-5, atol=1e-3)
     mass = out["mass"].cpu().numpy().astype(np.float64)
     assert (np.abs(mass - ref["mass"]) / np.maximum(ref["mass"], 1.0)).max() <= 1e-3
+
+
+@pytest.mark.parametrize("block,k,d,H", [(32, 8, 128, 6), (64, 4, 128, 32), (128, 3, 64, 32), (32, 65, 64, 34)])
+def test_probabilities_are_relative_to_the_head_of_the_list(block, k, d, H):
+    """bf16: the probabilities are rounded relative to the largest score among the first 32 keys of a row's
+    list, wherever the walk over the rest of the list begins (the sink, if it is there, is then exactly 1).
+    Computed here in 64 bits with that rounding: all but the elements at a rounding boundary are equal."""
+    T = 32 * 128
+    w = wl.scaled(wl.config(2), (T,), topk=k, heads=H, kv_heads=1, block=block, head_dim=d, needles_per_kv_head=2)
+    Q, K, V, _ = wl.make_inputs(w)
+    N, subs = T // block, 2 if block == 128 else 1
+    assert H * N * subs > 60 * k * block // 32                     # rows of their own, not shared ones
+    g = torch.Generator().manual_seed(1)
+    idx = torch.full((H, N, k), -1, dtype=torch.int32)
+    for h in range(H):
+        for q in range(N):
+            some = torch.randperm(q - 1, generator=g)[:k - 2] + 1 if q > 1 else torch.empty(0, dtype=torch.long)
+            ids = torch.cat([torch.tensor([0]), some, torch.tensor([q])]).unique()
+            idx[h, q, :len(ids)] = ids.int()
+    cnt = (idx >= 0).sum(2).int()
+    scale = 1.0 / math.sqrt(d)
+    print(f"[attn] head of the list b={block} k={k} H={H}", flush=True)
+    out = binding.stream_sparse_attn(Q.to(DEV), K.to(DEV), V.to(DEV), H, 1, block, idx.to(DEV), cnt.to(DEV), scale)["O"]
+    torch.cuda.synchronize()
+    differing = 0
+    t = torch.arange(T, device=DEV)
+    Kd, Vd = K[0].to(DEV).double(), V[0].to(DEV).double()
+    for h in range(H):
+        keep = torch.zeros(N, N + 1, dtype=torch.bool, device=DEV)
+        e = idx[h].long().to(DEV)
+        keep.scatter_(1, torch.where(e < 0, N, e), True)
+        m = keep[:, :N].repeat_interleave(block, 0).repeat_interleave(block, 1) & (t[None, :] <= t[:, None])
+        S = (Q[h].to(DEV).double() @ Kd.T).mul_(scale * math.log2(math.e)).masked_fill_(~m, -math.inf)
+        P = torch.exp2(S - S[:, :32].amax(1, keepdim=True)).to(torch.bfloat16).double()
+        ref = (P @ Vd) / P.sum(1, keepdim=True)
+        differing += int((ref.to(torch.bfloat16) != out[h]).sum())
+    # fp32 sums of up to 2 k products and fp32 scores: about 1e-6 of the value, against boundaries 2^-8 apart
+    assert differing <= 0.01 * H * T * d, differing / (H * T * d)
 
 
 def test_strided_inputs_and_output():
