@@ -123,6 +123,7 @@ struct AttnParams {
     const unsigned *cbits, *call;
     long long cpitch;
     int cw;
+    unsigned sweep;              // workgroups an XCD starts while a row walks its list (not SPLIT): see phase_sweep
     WgMap map;
     SeqTable seqs;
 };
@@ -178,14 +179,18 @@ __device__ __forceinline__ float dot2_ones(unsigned pair, float acc)
 // ARB: the mask C is an explicit bit array (STREAM_MASK_ARRAY).  WIDE: lists of more than 64 entries
 // (up to kMaxTopkWide) sit in LDS instead of one register.  SPLIT: the four wavefronts of a workgroup
 // share one row, wavefront w taking the sub-tiles w, w + 4, ... (else a wavefront has a row of its own).
-template <bool ARB, bool WIDE, bool SPLIT>
+// SHIFT: the walk over the list is shifted (rows in phase, see attn_row).
+template <bool ARB, bool WIDE, bool SPLIT, bool SHIFT>
 struct AttnRow {
     int lane, wave;
     int h, kvh, gb, q, L, qtok0, qt;            // head, kv head, global / local query block, length, first query, queries
     int blk0, nblk;
     long long tok0;
+    const int *idx;                             // the row's list in memory
+    int kmax, bq;
     int mask, window, ksh;
     int my_blk;                                 // lane j holds list entry j (not WIDE)
+    int n_blk;                                  // entries of the list
     int *blk;                                   // this wavefront's list in LDS (WIDE)
     int n_tiles;                                // 32-key sub-tiles of the row's list that can hold a visible key
     int rot;                                    // sub-tiles by which the walk behind the list's first one is shifted (< n_tiles)
@@ -197,7 +202,7 @@ struct AttnRow {
     {
         int ts = __builtin_amdgcn_readfirstlane(t);
         ts = ts < n_tiles ? ts : n_tiles - 1;
-        if constexpr (SPLIT) return ts;
+        if constexpr (!SHIFT) return ts;
         // the head of the list first, then from `rot` on and around the end
         const int tr = ts + rot;
         return ts == 0 ? 0 : (tr < n_tiles ? tr : tr - (n_tiles - 1));
@@ -232,10 +237,10 @@ struct AttnRow {
     }
 };
 
-// Fills in the row; false: nothing to do.  (SPLIT: the same answer in all four wavefronts.)
-// in_flight: workgroups of this kernel an XCD runs at a time (32 CUs x wavefronts per SIMD).
-template <bool ARB, bool WIDE, bool SPLIT>
-__device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, unsigned in_flight, int *lds_list, AttnRow<ARB, WIDE, SPLIT> &r)
+// Fills in the row and issues the loads of its list; false: nothing to do.  (SPLIT: the same answer in all four
+// wavefronts.)
+template <bool ARB, bool WIDE, bool SPLIT, bool SHIFT>
+__device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, int *lds_list, AttnRow<ARB, WIDE, SPLIT, SHIFT> &r)
 {
     r.lane = threadIdx.x & 63;
     r.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keep it scalar
@@ -284,14 +289,28 @@ __device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, unsigned i
     r.qtok0 = r.q * a_b + qs * qt;                // first query token (sequence-local) of this row
     if (r.qtok0 >= r.L) return false;
     const long long row = (long long)r.h * a_NB + gb;
-    const int *my_idx = a_idx + row * a_kmax;
+    r.idx = a_idx + row * a_kmax;
+    r.kmax = a_kmax; r.bq = a_b;
     // (the list is fetched for every slot of the row, whatever its count, so that the load does
     // not wait for the count)
-    const int my_raw = !WIDE && r.lane < a_kmax ? my_idx[r.lane] : 0;
-    int n_blk = a_cnt[row];
-    n_blk = n_blk < 0 ? 0 : (n_blk > a_kmax ? a_kmax : n_blk);   // never read past the row's list
-    r.my_blk = r.lane < n_blk ? my_raw : 0;
+    r.my_blk = !WIDE && r.lane < a_kmax ? r.idx[r.lane] : 0;
+    r.n_blk = a_cnt[row];
     r.blk = lds_list;
+    return true;
+}
+
+// Second half, after the kernel has issued its loads of Q: this waits for the list.  (In one piece the wait
+// came ahead of the loads of Q: pass 1 378 instead of 369 us at 10 k tokens and k = 256, pass 2 2.39 instead of
+// 2.37 ms at 131 k.)
+template <bool ARB, bool WIDE, bool SPLIT, bool SHIFT>
+__device__ __forceinline__ void attn_list(const AttnParams &p, AttnRow<ARB, WIDE, SPLIT, SHIFT> &r)
+{
+    __builtin_amdgcn_sched_barrier(0);
+    const int a_kmax = r.kmax, a_b = r.bq, qt = r.qt, gb = r.gb, nblk = r.nblk;
+    const int *my_idx = r.idx;
+    int *lds_list = r.blk;
+    const int n_blk = r.n_blk < 0 ? 0 : (r.n_blk > a_kmax ? a_kmax : r.n_blk);   // never read past the row's list
+    if (r.lane >= n_blk) r.my_blk = 0;
     // ARB: "every pair of this query block and that key block is real and set in C", per key block
     const unsigned *allrow = ARB ? p.call + (long long)gb * p.cw : nullptr;
     auto all_bit = [&](int e) -> bool {           // (an entry outside the block range reads as "cut")
@@ -303,7 +322,7 @@ __device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, unsigned i
     // token-level mask (so no key after a query, and no key outside the sequence, ever
     // counts), and the trimming of the last block is skipped.
     const int bk = 32 << r.ksh, ksub = 1 << r.ksh;
-    const int nkb = (int)((long long)sd.nblk * a_b / bk);         // key blocks of the sequence
+    const int nkb = (int)((long long)nblk * a_b / bk);            // key blocks of the sequence
     bool entry_bad = false;
     if constexpr (WIDE) {
         for (int i = r.lane; i < n_blk; i += 64) {
@@ -336,26 +355,23 @@ __device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, unsigned i
     // An XCD works on the keys of one kv head at a time, far more than its L2 holds, and what a row
     // finds there is what other rows in flight have just read.  Rows start one after the other, so if each
     // began at the head of its list they would be spread over the whole key axis at any moment.
-    // Instead row i of the R an XCD has in flight goes, after the first sub-tile, to i/R of the way through
-    // its list and wraps around: a full sweep takes as long as R rows take to be started, so all rows in
-    // flight pass the same keys at the same time.  The first sub-tile of the list stays the first one visited:
-    // it usually holds the heaviest key (the sink), whose probability is then 1 before it is rounded to
+    // Instead workgroup i of the R that an XCD starts while a row lasts goes, after the first sub-tile, to
+    // i/R of the way through its list and wraps around: a full sweep takes as long as R workgroups take to be
+    // started, so all rows in flight pass the same keys at the same time (phase_sweep says what R is and what
+    // it measured).  The first sub-tile of the list stays the first one visited: it usually holds the heaviest key (the sink), whose probability is then 1 before it is rounded to
     // bf16.  (From i/R on without it: error of O against 64 bits 1.85e-3 instead of 1.81e-3 at 10 k tokens, of the
     // mass 4.1e-7 instead of 3.1e-7; time the same.)  The order of the sums depends on the row's place in
     // the launch: O and lse repeat from call to call, not from one number of heads or packing to another.
-    // The mass is added up with atomics, in no fixed order.  131 k tokens, 32/8 heads, k = 32: requests
-    // of pass 1 that miss the L2 55 % -> 38 %, pass 1 5.40 -> 4.71 ms, pass 2 2.54 -> 2.41 ms; with half or
-    // twice the true R 5.72 and 5.08 ms; where a list has a handful of blocks or the keys fit the L2, no change.
+    // The mass is added up with atomics, in no fixed order.
     r.rot = 0;
-    if constexpr (!SPLIT) {
-        const unsigned phase = (blockIdx.x / kXcds) % in_flight;
-        const int rot = (int)(((unsigned)n_blk * phase / in_flight) << r.ksh);
+    if constexpr (SHIFT) {
+        const unsigned phase = (blockIdx.x / kXcds) % p.sweep;
+        const int rot = (int)(((unsigned)n_blk * phase / p.sweep) << r.ksh);
         r.rot = __builtin_amdgcn_readfirstlane(rot < n_tiles ? rot : (n_tiles > 0 ? n_tiles - 1 : 0));
     }
     // ARB: one lane per entry looks its block up once, the loops then test a scalar bit per sub-tile
     r.allmask = 0;
     if constexpr (ARB && !WIDE) r.allmask = __ballot(r.lane < n_blk && all_bit(r.my_blk));
-    return true;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -404,9 +420,9 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
     __shared__ int s_blk[WIDE ? 4 : 1][WIDE ? kMaxTopkWide : 1];
     __shared__ float s_ml[SPLIT ? 4 : 1][3][SPLIT ? QT : 1];   // SPLIT: reference, sum, sum of rounded per query
 
-    AttnRow<ARB, WIDE, SPLIT> r;
+    AttnRow<ARB, WIDE, SPLIT, !SPLIT> r;
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (!attn_row(p, QT, OCC == 1 ? 32u : NQ == 1 ? 96u : 64u, s_blk[WIDE ? wave_id : 0], r)) return;
+    if (!attn_row(p, QT, s_blk[WIDE ? wave_id : 0], r)) return;
     const int lane = r.lane, wave = r.wave;
     const int col = lane & 31, gh = lane >> 5;
     const int L = r.L, qtok0 = r.qtok0;
@@ -437,6 +453,7 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
 #pragma unroll
             for (int fr = 0; fr < FR; ++fr) v[cq][fr] = __builtin_amdgcn_raw_buffer_load_b128(qrs, voff + fr * 32, 0, 0);
         }
+        attn_list(p, r);
 #pragma unroll
         for (int cq = 0; cq < NQ; ++cq)
 #pragma unroll
@@ -809,9 +826,9 @@ __global__ void __launch_bounds__(256, OCC) attn_mass_kernel(const AttnParams p)
     constexpr int TS = SPLIT ? 4 : 1;
     __shared__ int s_blk[WIDE ? 4 : 1][WIDE ? kMaxTopkWide : 1];
 
-    AttnRow<ARB, WIDE, SPLIT> r;
+    AttnRow<ARB, WIDE, SPLIT, !SPLIT && NQ == 1> r;        // (64-query rows gain nothing from a shift here)
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (!attn_row(p, QT, OCC == 1 ? 32u : NQ == 1 ? 128u : 64u, s_blk[WIDE ? wave_id : 0], r)) return;
+    if (!attn_row(p, QT, s_blk[WIDE ? wave_id : 0], r)) return;
     const int lane = r.lane;
     const int col = lane & 31, gh = lane >> 5;
     const int L = r.L, qtok0 = r.qtok0;
@@ -851,6 +868,7 @@ __global__ void __launch_bounds__(256, OCC) attn_mass_kernel(const AttnParams p)
                 lq[rq][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(lrs, voff, 0, 0));
             }
     }
+    attn_list(p, r);
     float *mass_h = p.mass + (long long)r.h * p.T + r.tok0;
     const int n_tiles = r.n_tiles, t0 = SPLIT ? r.wave : 0;
     uint4 kreg[FR];
@@ -927,25 +945,89 @@ __global__ void __launch_bounds__(256, OCC) attn_mass_kernel(const AttnParams p)
 
 typedef void (*attn_fn)(const AttnParams);
 
+// A kernel and the workgroups of it that a CU runs at a time.
+struct AttnKernel {
+    attn_fn fn;
+    int (*per_cu)();
+};
+
+// What the kernel's registers and LDS leave room for (a workgroup is one wavefront per SIMD): asked of the
+// runtime once per kernel, a property of the compiled code.  Pass 1 bf16 with 32-query rows fits two at d = 128
+// and four at d = 64, pass 2 up to five, fp32 with d = 128 one.
+template <attn_fn FN>
+static int attn_per_cu()
+{
+    static const int n = [] {
+        int wgs = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&wgs, FN, 256, 0) != hipSuccess || wgs < 1) {
+            (void)hipGetLastError();
+            wgs = 2;
+        }
+        return wgs;
+    }();
+    return n;
+}
+
+// R of the rows in phase (see attn_row).  A launch starts with all its workgroups at once, in phase without any
+// shift, and drifts apart, because of the wavefronts of a SIMD one is served first: once the starts are
+// spread evenly R is what an XCD has in flight, before that a shift of 1/R puts rows out of phase that were in
+// it, and with one wavefront per SIMD they stay in it.  Pass 1, us, without shift / R in flight / this rule:
+// two per SIMD, 32/8 heads, 131 k tokens at k = 32 5523 / 4800 / 4800 (2048 workgroups per XCD; requests that
+// miss the L2 55 % -> 38 %), 80 k 2841 / 2758 / 2760 (1280), 12/2 heads 60 k at k = 64 1473 / 1585 / 1466 (703),
+// blocks of 32, 30 k at k = 256 1516 / 1725 / 1512 (352); four per SIMD (d = 64), 60 k at k = 64 1414 / 1333 / 1333
+// (1875), 120 k 5443 / 4337 / 4337 (1407); one per SIMD, 60 k at k = 256 3506 / 6982 / 3321 (703), 131 k, k = 64
+// 6824 / 10596 / 6801 (4096).  Where the keys fit the L2 nothing changes.  In pass 2, 131 k tokens:
+// 64-query rows 2.37 ms with the shift, 2.34 without, 32-query rows (k = 64) 3.5 and 3.9.  fp32 is walked without a shift: its
+// products take eight times as long per byte (d = 64, 60 k at k = 256 10336 / 11201 / 10950, at k = 64 2827 / 2911 /
+// 2870; 30 k the same either way).
+static unsigned phase_sweep(bool bf16, int per_cu, int grid)
+{
+    if (!bf16) return 1;
+    const unsigned started = (unsigned)(grid + kXcds - 1) / kXcds;        // workgroups of an XCD
+    const unsigned in_flight = per_cu > 1 ? 32u * (unsigned)per_cu : 192u;
+    const unsigned early = (1u << 17) / (started ? started : 1u);
+    return early > in_flight ? early : in_flight;
+}
+
+// Long lists of 32-query rows over more keys than the L2 holds a good part of: one workgroup per CU, by way of
+// LDS that nobody uses.  Two wavefronts on a SIMD drift apart and with them the rows that should pass the same
+// keys together; half as many, in step, read less from beyond the L2.  Pass 1 (bf16, d = 128), us, two / one:
+// 12/2 heads, 60 k tokens at k = 256 5022 / 3321, at k = 64 1046 / 994, 40 k at k = 256 2234 / 2067, at k = 64 671 /
+// 677, 32/8 heads, 131 k at k = 64 7295 / 6791; the other way round 30 k at k = 256 1540 / 1567, at k = 64 478 / 497,
+// 32/8 heads 60 k at k = 32 1549 / 1611, 40 k at k = 16 583 / 641; 64-query rows 1466 / 1601 (60 k at k = 64),
+// d = 64 1372 / 1455.
+constexpr unsigned kOneWgPerCuLds = 48 << 10;             // (with the kernel's own 34 KB: more than half of 160 KB)
+
+static bool one_wg_per_cu(const Problem &pb, int topk_max)
+{
+    return pb.b == 32 && pb.d == 128 && pb.dtype == STREAM_BF16 && topk_max >= 64 &&
+           2LL * pb.T * pb.d * pb.esize / pb.batch >= 20000000;
+}
+
+template <attn_fn FN>
+static AttnKernel attn_kernel() { return AttnKernel{FN, attn_per_cu<FN>}; }
+
 // Wavefronts own 64 queries of a row (32 for query block 32).  fp32 with d = 128 fits one wavefront per
 // SIMD only.
 template <bool BF16, int D, int NQ, bool ARB, bool WIDE>
-static attn_fn pick_attn(int pass, bool split)
+static AttnKernel pick_attn(int pass, bool split)
 {
     constexpr int OCC = BF16 || D == 64 ? 2 : 1;
     if (pass == 1)
-        return split ? attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, true> : attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, false>;
-    return split ? attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, true> : attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, false>;
+        return split ? attn_kernel<attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, true>>()
+                     : attn_kernel<attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, false>>();
+    return split ? attn_kernel<attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, true>>()
+                 : attn_kernel<attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, false>>();
 }
 
 template <bool BF16, int D, int NQ>
-static attn_fn pick_attn_list(int pass, bool split, bool arb, bool wide)
+static AttnKernel pick_attn_list(int pass, bool split, bool arb, bool wide)
 {
     if (arb) return wide ? pick_attn<BF16, D, NQ, true, true>(pass, split) : pick_attn<BF16, D, NQ, true, false>(pass, split);
     return wide ? pick_attn<BF16, D, NQ, false, true>(pass, split) : pick_attn<BF16, D, NQ, false, false>(pass, split);
 }
 
-static attn_fn pick_attn_kernel(const Problem &pb, int pass, bool split)
+static AttnKernel pick_attn_kernel(const Problem &pb, int pass, bool split)
 {
     const bool arb = pb.mask == STREAM_MASK_ARRAY;
     const bool wide = pb.kmax > kMaxTopk;              // lists longer than one register of entries
@@ -1080,7 +1162,10 @@ stream_status stream_sparse_attn(const void *Q, const void *K, const void *V,
         const long long per_kv = split ? items_per_kv : (items_per_kv + 3) / 4;
         if (per_kv * pb.Hkv + 64 > 0x7fffffffLL) return STREAM_EUNSUPPORTED;
         p.map = make_wg_map(pb.Hkv, (int)per_kv);
-        hipLaunchKernelGGL(pick_attn_kernel(pb, pass, split), dim3((unsigned)p.map.grid), dim3(256), 0, st, p);
+        const AttnKernel k = pick_attn_kernel(pb, pass, split);
+        const bool one = pass == 1 && !split && one_wg_per_cu(pb, topk_max);
+        p.sweep = split ? 1u : phase_sweep(pb.dtype == STREAM_BF16, one ? 1 : k.per_cu(), p.map.grid);
+        hipLaunchKernelGGL(k.fn, dim3((unsigned)p.map.grid), dim3(256), one ? kOneWgPerCuLds : 0u, st, p);
         if (hipGetLastError() != hipSuccess) return STREAM_EDEVICE;
     }
     return STREAM_OK;

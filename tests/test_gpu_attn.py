@@ -171,6 +171,42 @@ def test_probabilities_are_relative_to_the_head_of_the_list(block, k, d, H):
     assert differing <= 0.01 * H * T * d, differing / (H * T * d)
 
 
+def test_long_lists_over_many_keys_run_one_workgroup_per_cu():
+    """32-query rows, lists of 64 slots, 20 MB of keys and values per kv head: the launch that leaves one
+    workgroup on a CU.  The same lists in 63 slots take the other one; an explicit causal array the masked form."""
+    T, H, d, b = 40000, 6, 128, 32
+    N = T // b
+    g = torch.Generator(device=DEV).manual_seed(2)
+    Q = torch.randn((H, T, d), generator=g, device=DEV).to(torch.bfloat16)
+    K, V = (torch.randn((1, T, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    q = torch.arange(N, device=DEV)
+    some = (torch.rand((H, N, 61), generator=g, device=DEV) * (q[:, None] + 1)).int()
+    ids = torch.cat([torch.zeros(H, N, 1, device=DEV).int(), some, q.int().expand(H, N)[..., None]], 2).sort(2).values
+    again = torch.zeros_like(ids, dtype=torch.bool)
+    again[..., 1:] = ids[..., 1:] == ids[..., :-1]
+    ids = torch.where(again, N, ids).sort(2).values
+    cnt = (ids < N).sum(2).int().contiguous()
+    idx = torch.where(ids < N, ids, -1).contiguous()
+    wide = torch.cat([idx, torch.full((H, N, 1), -1, dtype=torch.int32, device=DEV)], 2).contiguous()
+    assert H * N > 60 * 64 and 2 * T * d * 2 >= 20e6
+    bits = torch.zeros((T, T // 32), dtype=torch.int32, device=DEV)
+    t = torch.arange(T, device=DEV)
+    word = torch.arange(T // 32, device=DEV)
+    bits[word[None, :] < (t >> 5)[:, None]] = -1
+    own = (2 << (t & 31)) - 1
+    bits[t, t >> 5] = torch.where(own >= 1 << 31, own - (1 << 32), own).int()
+    scale = 1.0 / math.sqrt(d)
+    got = []
+    for lists, kw in ((idx, {}), (wide, {}), (wide, dict(mask="array", mask_bits=bits))):
+        print(f"[attn] one workgroup per CU: slots {lists.shape[2]} {list(kw)}", flush=True)
+        got.append(binding.stream_sparse_attn(Q, K, V, H, 1, b, lists, cnt, scale, want_lse=True, want_mass=True, **kw))
+        torch.cuda.synchronize()
+    for other in got[1:]:
+        assert (other["O"].float() - got[0]["O"].float()).abs().max() <= TOL["bf16"]
+        assert (other["lse"] - got[0]["lse"]).abs().max() <= 1e-5
+        assert ((other["mass"] - got[0]["mass"]).abs() / got[0]["mass"].clamp(min=1.0)).max() <= 1e-5
+
+
 def test_strided_inputs_and_output():
     """Token-major [T, H, d] storage (one fused projection buffer) viewed as [H, T, d], for Q, K,
     V and the output: same results as the contiguous call, for the attention and for the
