@@ -9,6 +9,7 @@ import pytest
 import torch
 
 from oracle import receiver_stats as rs
+from paper_2510_19875_amd import binding
 from tests.test_gpu_receiver_stats import run
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +64,31 @@ def test_many_sequences_share_the_row_queue():
         np.testing.assert_array_equal(got["block_mean"][:, b0:b0 + nb, b0:b0 + nb], one["block_mean"])
         np.testing.assert_array_equal(got["head"][:, s], one["head"][:, 0])
         b0 += nb
+
+
+@pytest.mark.parametrize("b,dtype", [(64, torch.bfloat16), (32, torch.bfloat16), (64, torch.float32)])
+def test_error_against_64_bits(b, dtype):
+    """Block means are averages over b x b probabilities with an error of a few 1e-8 each from the scores and
+    exponentials; what the sums over a row and over a span add must stay below that.  The kurtosis of a column
+    amplifies the errors of its largest entries by about four."""
+    H, T, d = 4, 12288, 128
+    print(f"[error] b={b} {dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    Q, K = (torch.randn((H, T, d), generator=g, device="cuda") for _ in range(2))
+    K[:, 0] *= 4.0
+    Q, K = Q.to(dtype), K.to(dtype)
+    got = binding.stream_receiver_stats(Q, K, H, H, b, 1.0 / math.sqrt(d), want_block_mean=True)
+    N = T // b
+    t = torch.arange(T, device="cuda")
+    hidden = t[None, :] > t[:, None]
+    visible = torch.ones(N, N, dtype=torch.bool, device="cuda").tril()
+    n = visible.sum(0)
+    for h in range(H):
+        P = torch.softmax((Q[h].double() @ K[h].double().T / math.sqrt(d)).masked_fill_(hidden, -math.inf), 1)
+        M = P.view(N, b, N, b).mean((1, 3))
+        y = torch.where(visible, M - M.sum(0) / n, 0.0)
+        kurt = torch.where(n >= 4, (y ** 4).sum(0) / n / ((y ** 2).sum(0) / n).clamp(min=1e-300) ** 2 - 3.0, 0.0)
+        err = lambda a, w: float((a.double() - w).norm() / w.norm())
+        e = err(got["block_mean"][h], M), err(got["col_kurt"][h], kurt)
+        print(f"[error] head {h} {e[0]:.2e} {e[1]:.2e}", flush=True)
+        assert e[0] <= 9e-8 and e[1] <= 2.8e-7
