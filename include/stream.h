@@ -342,8 +342,10 @@ stream_status stream_mask_diff(const int *idx_a, const int *cnt_a, const float *
  *   head_stats  float [heads, batch, 2]: [0] the maximum of col_kurt over the sequence's columns
  *               with at least 4 values (0 if there is none), [1] the excess kurtosis of
  *               col_mean over the sequence's columns that hold a real key (0 for fewer than 4)
- *   workspace   stream_receiver_stats_workspace_bytes(shape) bytes (packed K, a scratch row per
- *               wavefront in flight, span sums of a chunk of query blocks), 256-byte aligned
+ *   workspace   stream_receiver_stats_workspace_bytes(shape) bytes (packed K, span sums of a chunk of
+ *               query blocks and, up to 1 GiB or the size of Q, a scratch row per wavefront in flight),
+ *               256-byte aligned.  Where that is more than packed copies of Q and K and 4 bytes per
+ *               padded token and head, as much as those is enough too: the scores are then computed twice.
  * The moments are accumulated in fp64 from the fp32 block means.  Errors: as stream_prune;
  * STREAM_EUNSUPPORTED also for dtype F32 with head_dim 128 and b_k = 128.  With STREAM_MASK_ARRAY a
  * query that sees no key has a zero row of probabilities, and a key block no query block sees is

@@ -10,7 +10,8 @@
 // the sums into means and adds up their powers per column, in fp64 and shifted by the column's first
 // value; a third, tiny one reduces the column statistics to the two numbers per (head, sequence).
 // Memory O(T): the scratch belongs to the wavefronts in flight, and the sums are kept for a chunk of
-// query blocks at a time.
+// query blocks at a time.  Where the workspace has no room for the scratch every score is computed twice
+// instead: once for the normalisers, once more for the spans.
 #include "stream_mfma.h"
 
 #include <math.h>
@@ -20,7 +21,7 @@ namespace stream {
 struct StatsParams {
     const char *Q, *Kp;         // Q as given; K packed fragments [kv_heads][global block][b * d]
     long long q_sh_b, q_st_b;   // byte strides of Q (head, token)
-    float *scratch;             // per wavefront of the row kernel: scratch_wave floats
+    float *scratch;             // per wavefront of the row kernel: scratch_wave floats (nullptr: none, see below)
     long long scratch_wave;
     float *sums;                // [heads, (qb1 - qb0) * subs, NBk]: span sums of this chunk, per query tile
     int *queue;                 // [kXcds]: row groups handed out so far (zero before the first chunk, zeroed by the second kernel)
@@ -69,6 +70,7 @@ __host__ __device__ __forceinline__ void mask_irange(int mask, int window, int j
 // ARB: the mask is an explicit bit array: the tiles between the first and the last key block the
 // query block sees are streamed and every element takes its bit (a lane owns a query: one mask word
 // per 32 keys).  A query that sees no key has a zero row of probabilities.
+// SCRATCH: the sums per query wait in scratch for the normalisers; else the scores are computed twice.
 //
 // Per element one fused multiply-add, one exp2 (8 cycles) and one add, besides 16 cycles of MFMA for 16
 // of them: vector ALU and matrix core are about equally loaded, so two wavefronts share a SIMD.  With the
@@ -87,7 +89,7 @@ __host__ __device__ __forceinline__ void mask_irange(int mask, int window, int j
 // query tile, which read the same keys) from a queue per XCD, longest first.  (Dealt out beforehand, 8
 // per workgroup and equally long in sum, they left SIMDs with one wavefront for the last third of the
 // launch: of two wavefronts on a SIMD one is served first and ends first.)
-template <bool BF16, int D, int NS, int OCC, bool ARB, bool BK32>
+template <bool BF16, int D, int NS, int OCC, bool ARB, bool BK32, bool SCRATCH>
 __global__ void __launch_bounds__(256, OCC) stats_rows_kernel(const StatsParams p)
 {
     constexpr int ES = BF16 ? 2 : 4;
@@ -100,7 +102,7 @@ __global__ void __launch_bounds__(256, OCC) stats_rows_kernel(const StatsParams 
     const unsigned lane_off = lane * 16;
     const int subs = p.b / QT;                      // query tiles per block
     const long long items_per_kv = (long long)(p.qb1 - p.qb0) * subs * p.g;
-    float *scr = p.scratch + ((long long)blockIdx.x * 4 + wave) * p.scratch_wave;
+    float *scr = SCRATCH ? p.scratch + ((long long)blockIdx.x * 4 + wave) * p.scratch_wave : nullptr;
     // (a workgroup stays on the kv heads of its XCD)
     __shared__ int s_next;
     const int xcd = blockIdx.x % kXcds;
@@ -174,11 +176,14 @@ __global__ void __launch_bounds__(256, OCC) stats_rows_kernel(const StatsParams 
         }
         float m[NS];                                    // reference per query (log2 domain)
         double l = 0.0;                                 // lane t: sum of query t's exponentials (NS == 1: lanes below 32)
+        float inv = 0.f;                                // ... and 1 / l
 #pragma unroll
         for (int qs = 0; qs < NS; ++qs) m[qs] = -INFINITY;
-        // 0: first attempt, references set on the way; 1: true maxima only; 2: references given
-        for (int mode = 0; mode < 3; ++mode) {
-            l = 0.0;
+        // 0: first attempt, references set on the way; 1: true maxima only; 2: references given; 3 (no
+        // scratch): references and normalisers given, the spans' sums are formed tile by tile
+        for (int mode = 0;;) {
+            float span = 0.f;                           // mode 3: sum of the span so far (blocks of 128 keys: two tiles)
+            if (mode < 3) l = 0.0;
             bool track = mode == 0;                     // wave-uniform: some query has no reference yet
             uint4 kf[2][FR];
 #pragma unroll
@@ -282,20 +287,36 @@ __global__ void __launch_bounds__(256, OCC) stats_rows_kernel(const StatsParams 
                         v = BK32 ? part[rr][0] : part[0][0] + part[1][0];
                         v += __shfl_xor(v, 32);
                     }
+                    if (!SCRATCH && mode == 3) {
+                        const int j = p.bk == 32 ? kt * 2 + rr : (p.bk == 64 ? kt : kt >> 1);
+                        const float sum = wave_sum(NS == 2 || lane < 32 ? v * inv : 0.f);
+                        span = (p.bk == 128 && (kt & 1)) ? span + sum : sum;
+                        if (lane == 0 && j >= j_lo && j <= j_hi) sums[j] = span;
+                        continue;
+                    }
                     l += (double)v;
-                    if (NS == 2 || lane < 32) scr[((kt - kt_lo) * RPT + rr) * QT + (NS == 2 ? lane : lane & 31)] = v;
+                    if (SCRATCH && (NS == 2 || lane < 32)) scr[((kt - kt_lo) * RPT + rr) * QT + (NS == 2 ? lane : lane & 31)] = v;
                 }
             }
-            if (mode == 1) continue;
+            if (!SCRATCH && mode == 3) break;
+            if (mode == 1) { mode = 2; continue; }
             bool seen = m[0] != -INFINITY;
             if constexpr (NS == 2) seen = lane < 32 ? m[0] != -INFINITY : m[1] != -INFINITY;
-            if (mode == 2 || !__any(seen & (!(l > 1e-30) | !(l < 3e38)))) break;
+            if (mode == 0 && __any(seen & (!(l > 1e-30) | !(l < 3e38)))) { mode = 1; continue; }
+            inv = l == 0.0 ? 0.f : (float)(1.0 / l);    // (a NaN stays one)
+            if (SCRATCH) break;
+            mode = 3;
+        }
+        if constexpr (!SCRATCH) {
+            const int jf = (int)((long long)kt_lo * 64 / p.bk), jl = (int)(((long long)kt_hi * 64 + 63) / p.bk);
+            for (int j = j_lo + lane; j <= j_hi; j += 64)
+                if (j < jf || j > jl) sums[j] = 0.f;    // blocks these queries do not reach
+            continue;
         }
 
         // span sums of the normalised probabilities: lane j of a chunk of 64 key blocks reads the row of
         // its block from the scratch (all of a row's 64 queries, four at a time)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        const float inv = l == 0.0 ? 0.f : (float)(1.0 / l);    // (a NaN stays one)
         const int nrows = (kt_hi - kt_lo + 1) * RPT, ksub = p.bk > 64 ? 2 : 1;
         for (int j0 = j_lo; j0 <= j_hi; j0 += 64) {
             const int j = j0 + lane;
@@ -474,45 +495,65 @@ __global__ void __launch_bounds__(256) stats_zero_kernel(float *p, long long n)
 }
 
 struct StatsWorkspace {
+    bool scratch_rows;           // one pass over the scores
     size_t kp, queue, scratch, sums, state, cany, call, coln, total;
     long long scratch_wave;      // floats per wavefront of the row kernel
     int wgs;                     // workgroups of the row kernel
     int chunk;                   // query blocks per chunk
 };
 
-// Workgroups of the row kernel: what the chip holds (2 wavefronts per SIMD; 3 with 32 queries each, 1 with
-// fp32 at d = 128).  32 k tokens, 32/8 heads: rows 4.40 ms (1.0 PFLOP/s
+// Workgroups of the row kernel that the chip holds: 2 wavefronts per SIMD; 3 with 32 queries each (but an array
+// and 128 bytes or more a row take the registers of the third), 1 with fp32 at d = 128.  32 k tokens, 32/8
+// heads: rows 4.40 ms (1.0 PFLOP/s
 // of scores), columns 74 us; two thirds of that time are what the MFMAs alone take at the clock the power
 // limit leaves (0.64 us per tile and SIMD, 0.92-0.97 with the exponentials and nothing else, 1.07 here).
 static int stats_wgs(const Problem &pb)
 {
     if (pb.dtype == STREAM_F32 && pb.d == 128) return 256;
-    return pb.b == 32 ? 768 : 512;
+    const bool third = pb.b == 32 && (pb.mask != STREAM_MASK_ARRAY || pb.d * pb.esize <= 128);
+    return third ? 768 : 512;
 }
 
 // Span sums kept at a time.  (A chunk is one launch of either kernel; 128 MiB are 512 query blocks at 131 k
 // tokens and 32 heads, several rounds of the row kernel's grid.)
 constexpr size_t kStatsSumsBytes = (size_t)128 << 20;
 
-static StatsWorkspace stats_layout(const Problem &pb)
+// Scratch rows are taken up to this size, or up to the size of Q: a wavefront's is as long as a row, whatever the
+// number of heads (one head of 131 k tokens 1 GiB, of 1 M tokens 8 GiB).  Beyond, or in a workspace that has
+// no room for them, the scores are computed twice (32 k tokens, 32/8 heads: 8.3 ms instead of 4.4).
+constexpr size_t kStatsScratchBytes = (size_t)1 << 30;
+
+static StatsWorkspace stats_layout_as(const Problem &pb, bool scratch_rows)
 {
     StatsWorkspace w;
     size_t off = 0;
     const size_t NBk = (size_t)pb.NB * pb.b / pb.bk, subs = pb.b == 128 ? 2 : 1;
+    const size_t q_bytes = (size_t)pb.H * pb.NB * pb.b * pb.d * pb.esize;
+    w.scratch_rows = scratch_rows;
     w.kp = off;   off += align_up((size_t)pb.Hkv * pb.NB * pb.b * pb.d * pb.esize, 256);
-    // a scratch row of 32 or 64 floats per 64 (b_k = 32: per 32) keys of the longest sequence
-    int longest = 0;
-    for (int i = 0; i < pb.seqs.n; ++i) longest = pb.seqs.d[i].len > longest ? pb.seqs.d[i].len : longest;
-    w.scratch_wave = (long long)((longest + 63) / 64) * (pb.bk == 32 ? 2 : 1) * (pb.b == 32 ? 32 : 64);
-    w.wgs = stats_wgs(pb);
     w.queue = off; off += 256;
-    w.scratch = off; off += align_up((size_t)w.wgs * 4 * w.scratch_wave * 4, 256);
+    // (without the scratch the whole stays below packed copies of Q and K)
     const size_t per_block = (size_t)pb.H * subs * NBk * 4;
-    size_t chunk = kStatsSumsBytes / per_block;
+    size_t chunk = (scratch_rows || q_bytes > kStatsSumsBytes ? kStatsSumsBytes : q_bytes) / per_block;
     chunk = chunk < 1 ? 1 : (chunk > (size_t)pb.NB ? (size_t)pb.NB : chunk);
     w.chunk = (int)chunk;
     w.sums = off; off += align_up(per_block * chunk, 256);
     w.state = off; off += w.chunk < pb.NB ? align_up((size_t)6 * pb.H * NBk * 8, 256) : 0;
+    // a scratch row of 32 or 64 floats per 64 (b_k = 32: per 32) keys that a row may see
+    const int qt = pb.b == 32 ? 32 : 64;
+    long long keys = 0;
+    for (int i = 0; i < pb.seqs.n; ++i) keys = pb.seqs.d[i].len > keys ? pb.seqs.d[i].len : keys;
+    long long tiles = (keys + 63) / 64;
+    if (pb.mask == STREAM_MASK_SLIDING && ((long long)pb.window + qt + 61) / 64 + 1 < tiles)
+        tiles = ((long long)pb.window + qt + 61) / 64 + 1;        // window + qt - 1 keys, from anywhere in a tile on
+    w.scratch_wave = tiles * (pb.bk == 32 ? 2 : 1) * qt;
+    // a workgroup per four rows of the longest chunk, as many as the chip holds at the most
+    const long long row_items = (long long)chunk * (pb.b / qt) * pb.g;
+    const int full = (make_wg_map(pb.Hkv, (int)((row_items + 3) / 4)).grid + kXcds - 1) / kXcds * kXcds;
+    w.wgs = full < stats_wgs(pb) ? full : stats_wgs(pb);
+    const size_t scratch_bytes = align_up((size_t)w.wgs * 4 * w.scratch_wave * 4, 256);
+    if (scratch_rows && scratch_bytes > kStatsScratchBytes && scratch_bytes > q_bytes) return stats_layout_as(pb, false);
+    w.scratch = off; off += scratch_rows ? scratch_bytes : 0;
     // with a mask array: its block-level summaries and the number of spans of every column
     const bool arb = pb.mask == STREAM_MASK_ARRAY;
     const size_t bm = arb ? align_up((size_t)pb.NB * block_bitmap_words(pb) * 4, 256) : 0;
@@ -523,25 +564,41 @@ static StatsWorkspace stats_layout(const Problem &pb)
     return w;
 }
 
+// The layout to ask for.
+static StatsWorkspace stats_layout(const Problem &pb) { return stats_layout_as(pb, true); }
+
+// The layout for a workspace of `bytes` (its total is larger: refused).  Packed copies of Q and K and 4 bytes per
+// padded token and head are enough for the one without scratch rows.
+static StatsWorkspace stats_layout_in(const Problem &pb, size_t bytes)
+{
+    const StatsWorkspace w = stats_layout(pb);
+    const StatsWorkspace small = stats_layout_as(pb, false);
+    const size_t tokens = (size_t)pb.NB * pb.b;
+    const size_t copies = align_up(pb.H * tokens * pb.d * pb.esize, 256) + align_up(pb.Hkv * tokens * pb.d * pb.esize, 256) +
+                          align_up(pb.H * tokens * 4, 256) + (small.total - small.cany);
+    return bytes < w.total && bytes >= copies ? small : w;
+}
+
 typedef void (*stats_fn)(const StatsParams);
 
-template <bool BF16, int D, int NS>
+template <bool BF16, int D, int NS, bool SCRATCH>
 static stats_fn pick_stats_rows(bool arb, bool bk32)
 {
     constexpr int OCC = (BF16 || D == 64) ? 2 : 1;   // fp32 with d = 128 holds 16 fragments per group
-    if (arb) return bk32 ? stats_rows_kernel<BF16, D, NS, OCC, true, true> : stats_rows_kernel<BF16, D, NS, OCC, true, false>;
-    return bk32 ? stats_rows_kernel<BF16, D, NS, OCC, false, true> : stats_rows_kernel<BF16, D, NS, OCC, false, false>;
+    if (arb) return bk32 ? stats_rows_kernel<BF16, D, NS, OCC, true, true, SCRATCH> : stats_rows_kernel<BF16, D, NS, OCC, true, false, SCRATCH>;
+    return bk32 ? stats_rows_kernel<BF16, D, NS, OCC, false, true, SCRATCH> : stats_rows_kernel<BF16, D, NS, OCC, false, false, SCRATCH>;
 }
 
+template <bool SCRATCH>
 static stats_fn pick_stats_rows_kernel(const Problem &pb)
 {
     const bool arb = pb.mask == STREAM_MASK_ARRAY, bk32 = pb.bk == 32, ns1 = pb.b == 32;
     if (pb.dtype == STREAM_BF16) {
-        if (pb.d == 128) return ns1 ? pick_stats_rows<true, 128, 1>(arb, bk32) : pick_stats_rows<true, 128, 2>(arb, bk32);
-        return ns1 ? pick_stats_rows<true, 64, 1>(arb, bk32) : pick_stats_rows<true, 64, 2>(arb, bk32);
+        if (pb.d == 128) return ns1 ? pick_stats_rows<true, 128, 1, SCRATCH>(arb, bk32) : pick_stats_rows<true, 128, 2, SCRATCH>(arb, bk32);
+        return ns1 ? pick_stats_rows<true, 64, 1, SCRATCH>(arb, bk32) : pick_stats_rows<true, 64, 2, SCRATCH>(arb, bk32);
     }
-    if (pb.d == 128) return ns1 ? pick_stats_rows<false, 128, 1>(arb, bk32) : pick_stats_rows<false, 128, 2>(arb, bk32);
-    return ns1 ? pick_stats_rows<false, 64, 1>(arb, bk32) : pick_stats_rows<false, 64, 2>(arb, bk32);
+    if (pb.d == 128) return ns1 ? pick_stats_rows<false, 128, 1, SCRATCH>(arb, bk32) : pick_stats_rows<false, 128, 2, SCRATCH>(arb, bk32);
+    return ns1 ? pick_stats_rows<false, 64, 1, SCRATCH>(arb, bk32) : pick_stats_rows<false, 64, 2, SCRATCH>(arb, bk32);
 }
 
 }  // namespace stream
@@ -576,7 +633,7 @@ stream_status stream_receiver_stats(const void *Q, const void *K, const stream_s
     if ((q_sh * pb.esize | q_st * pb.esize | k_sh * pb.esize | k_st * pb.esize) & 15) return STREAM_EINVAL;
     if (pb.dtype == STREAM_F32 && pb.d == 128 && pb.bk == 128) return STREAM_EUNSUPPORTED;
     const bool arb = pb.mask == STREAM_MASK_ARRAY;
-    const StatsWorkspace w = stats_layout(pb);
+    const StatsWorkspace w = stats_layout_in(pb, workspace_bytes);
     if (!workspace || ((uintptr_t)workspace & 255) || workspace_bytes < w.total) return STREAM_EWORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
     char *ws = (char *)workspace;
@@ -588,7 +645,7 @@ stream_status stream_receiver_stats(const void *Q, const void *K, const stream_s
     p.Q = (const char *)Q;
     p.q_sh_b = q_sh * pb.esize; p.q_st_b = q_st * pb.esize;
     p.Kp = ws + w.kp;
-    p.scratch = (float *)(ws + w.scratch); p.scratch_wave = w.scratch_wave;
+    p.scratch = w.scratch_rows ? (float *)(ws + w.scratch) : nullptr; p.scratch_wave = w.scratch_wave;
     p.sums = (float *)(ws + w.sums);
     p.queue = (int *)(ws + w.queue);
     p.state = w.chunk < pb.NB ? (double *)(ws + w.state) : nullptr;
@@ -621,7 +678,7 @@ stream_status stream_receiver_stats(const void *Q, const void *K, const stream_s
     if (hipGetLastError() != hipSuccess) return STREAM_EDEVICE;
 
     const int qt = pb.b == 32 ? 32 : 64;
-    stats_fn rows = pick_stats_rows_kernel(pb);
+    stats_fn rows = w.scratch_rows ? pick_stats_rows_kernel<true>(pb) : pick_stats_rows_kernel<false>(pb);
     for (int qb0 = 0; qb0 < pb.NB; qb0 += w.chunk) {
         p.qb0 = qb0;
         p.qb1 = qb0 + w.chunk < pb.NB ? qb0 + w.chunk : pb.NB;

@@ -250,3 +250,20 @@ def test_header_is_plain_c(tmp_path):
     src.write_text('#include "stream.h"\nint main(void) { stream_shape s; (void)s; return (int)STREAM_OK; }\n')
     subprocess.check_call([cc, "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror", "-fsyntax-only",
                            "-I", os.path.join(ROOT, "include"), str(src)])
+
+
+@pytest.mark.parametrize("H,Hkv,d,b,bk,T,mask,window", [
+    (1, 1, 128, 64, 64, 131072, "causal", 0), (1, 1, 128, 64, 64, 1 << 20, "causal", 0), (12, 2, 128, 32, 32, 20000, "causal", 0),
+    (32, 8, 128, 64, 64, 131072, "causal", 0), (1, 1, 64, 128, 32, 1 << 22, "full", 0), (1, 1, 128, 64, 64, 8192, "causal", 0),
+    (1, 1, 128, 64, 64, 131072, "sliding", 4096), (2, 2, 64, 32, 32, 1000, "causal", 0)])
+def test_receiver_stats_workspace_is_bounded(lib, H, Hkv, d, b, bk, T, mask, window):
+    """Packed K, the span sums of a chunk and at most 1 GiB of scratch rows, or the size of Q; few rows, or rows
+    that see a window only, take less."""
+    s = shape(heads=H, kv_heads=Hkv, head_dim=d, block=b, block_k=bk, T=T, mask=B.MASKS[mask], window=window)
+    got = lib.stream_receiver_stats_workspace_bytes(ctypes.byref(s))
+    pad = -(-T // max(b, bk)) * max(b, bk)
+    q, k = H * pad * d * 2, Hkv * pad * d * 2
+    rows = H * pad // min(b, 64)
+    row = (-(-T // 64) if mask != "sliding" else (window + 64) // 64 + 2) * 64 * 4 * (2 if bk == 32 else 1)
+    scratch = min((rows + 31) // 32 * 32 * row, max(q, 1 << 30))
+    assert k < got <= k + scratch + (128 << 20) + 12 * H * pad + 8192

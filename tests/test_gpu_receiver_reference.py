@@ -2,6 +2,7 @@
 a key.  Scores hundreds of octaves above it overflow the row's sums: the row is then run again with
 the true maxima.  Against the oracle, for each form of the row kernel, and for rows whose first tiles
 hide every key (window, mask array)."""
+import ctypes
 import math
 
 import numpy as np
@@ -64,6 +65,55 @@ def test_many_sequences_share_the_row_queue():
         np.testing.assert_array_equal(got["block_mean"][:, b0:b0 + nb, b0:b0 + nb], one["block_mean"])
         np.testing.assert_array_equal(got["head"][:, s], one["head"][:, 0])
         b0 += nb
+
+
+def packed_copies(H, Hkv, T, d, b, bk, esize, array=False):
+    """Bytes of packed copies of Q and K, 4 bytes per padded token and head, and a mask array's summaries."""
+    pad, up = -(-T // max(b, bk)) * max(b, bk), lambda x: -(-x // 256) * 256
+    n = up(H * pad * d * esize) + up(Hkv * pad * d * esize) + up(H * pad * 4)
+    if array:
+        n += 2 * up(pad // b * (-(-(pad // bk) // 32)) * 4) + up(H * (pad // bk) * 4)
+    return n
+
+
+@pytest.mark.parametrize("H,Hkv,T,d,b,bk,dtype,mask,steep", [
+    (1, 1, 9001, 128, 64, 64, torch.bfloat16, "causal", False),
+    (3, 1, 5003, 64, 32, 32, torch.bfloat16, "causal", True),
+    (2, 2, 4100, 64, 128, 32, torch.float32, "sliding", False),
+    (2, 1, 4100, 64, 32, 128, torch.bfloat16, "full", True),
+    (2, 2, 3900, 64, 128, 128, torch.bfloat16, "sliding", True),
+    (1, 1, 3001, 64, 64, 32, torch.bfloat16, "array", False),
+    (1, 1, 40003, 64, 32, 32, torch.bfloat16, "causal", False),      # the span sums come in chunks
+])
+def test_a_workspace_without_scratch_rows(H, Hkv, T, d, b, bk, dtype, mask, steep):
+    """Packed copies of Q and K are room enough, nothing beyond is written, and the results are those of the
+    workspace that the query asks for."""
+    print(f"[budget] H={H}/{Hkv} T={T} d={d} {b}x{bk} {dtype} {mask} steep={steep}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    Q, K = (torch.randn((n, T, d), generator=g, device="cuda") for n in (H, Hkv))
+    if steep:
+        Q[..., 0], K[..., 0] = 12.0, 0.0
+        K[:, 300:, 0] = 12.0 * d ** 0.5                              # 200 octaves above the first tiles
+    Q, K = Q.to(dtype), K.to(dtype)
+    kw = dict(mask=mask, window=3000 if mask == "sliding" else 0)
+    if mask == "array":
+        t = torch.arange(T)
+        from tests.test_gpu_mask_array import pack_bits
+        kw["mask_bits"] = pack_bits(((t[None, :] <= t[:, None]) & (t[None, :] // 900 == t[:, None] // 900)).numpy())
+    need = packed_copies(H, Hkv, T, d, b, bk, dtype.itemsize, mask == "array")
+    room = torch.full((need + 65536,), 0x5A, dtype=torch.uint8, device="cuda")
+    args = (Q, K, H, Hkv, b, 1.0 / math.sqrt(d))
+    shape, _ = binding.make_shape(H, Hkv, d, b, binding._dtype_code(Q), T, None, Q=Q, K=K, block_k=bk, **kw)
+    assert need < binding.load().stream_receiver_stats_workspace_bytes(ctypes.byref(shape))
+    small = binding.stream_receiver_stats(*args, want_block_mean=True, block_k=bk, workspace=room[:need], **kw)
+    large = binding.stream_receiver_stats(*args, want_block_mean=True, block_k=bk, **kw)
+    torch.cuda.synchronize()
+    assert bool((room[need:] == 0x5A).all())
+    # sums of 64 probabilities per query tile in another order, their arguments a few ulps apart
+    for key in ("block_mean", "col_mean"):
+        torch.testing.assert_close(small[key], large[key], rtol=2e-4 if steep else 2e-5, atol=1e-30)
+    for key in ("col_kurt", "head"):
+        torch.testing.assert_close(small[key], large[key], rtol=1e-2, atol=1e-2)
 
 
 @pytest.mark.parametrize("b,dtype", [(64, torch.bfloat16), (32, torch.bfloat16), (64, torch.float32)])
