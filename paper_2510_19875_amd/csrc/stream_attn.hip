@@ -38,16 +38,19 @@ struct PrepParams {
     long long k_sh_b, k_st_b, v_sh_b, v_st_b;
     int d, esize, b, NB;
     unsigned groups;             // 32-key groups of K (and of V)
+    unsigned first;              // workgroups of the launches before this one
     float *mass;                 // nullable
     long long mass_n;
     SeqTable seqs;
 };
 
 constexpr int kZeroPerWg = 2048;
+// (a launch holds fewer than 2^32 threads, 2^24 workgroups: from half of that on the preparation takes several)
+constexpr long long kPrepWgsPerLaunch = 1LL << 23;
 
 __global__ void __launch_bounds__(256) attn_prep_kernel(PrepParams p)
 {
-    const unsigned wg = blockIdx.x;
+    const unsigned wg = p.first + blockIdx.x;
     if (wg < p.groups) {
         pack_group(p.K, p.Kp, p.k_sh_b, p.k_st_b, p.d * p.esize, p.b, p.NB, 0, p.seqs, wg);
         return;
@@ -1130,8 +1133,12 @@ stream_status stream_sparse_attn(const void *Q, const void *K, const void *V,
         const long long grid = 2 * groups + (pp.mass_n + kZeroPerWg - 1) / kZeroPerWg;
         if (grid > 0x7fffffffLL) return STREAM_EUNSUPPORTED;
         pp.groups = (unsigned)groups;
-        hipLaunchKernelGGL(attn_prep_kernel, dim3((unsigned)grid), dim3(256), 0, st, pp);
-        if (hipGetLastError() != hipSuccess) return STREAM_EDEVICE;
+        for (long long first = 0; first < grid; first += kPrepWgsPerLaunch) {
+            const long long n = grid - first < kPrepWgsPerLaunch ? grid - first : kPrepWgsPerLaunch;
+            pp.first = (unsigned)first;
+            hipLaunchKernelGGL(attn_prep_kernel, dim3((unsigned)n), dim3(256), 0, st, pp);
+            if (hipGetLastError() != hipSuccess) return STREAM_EDEVICE;
+        }
     }
     AttnParams p;
     p.Q = (const char *)Q;

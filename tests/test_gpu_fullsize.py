@@ -191,3 +191,29 @@ def test_config5_ragged_reasoning_shape_sampled():
               f"max rel err {float(np.max(np.abs(m_gpu - m_ref) / np.maximum(m_ref, 1e-3))):.2e}, "
               f"all {len(gbs)} rows: max|dO|={O_err:.3e} max|dlse|={l_err:.3e}", flush=True)
         assert O_err <= 2e-2 and l_err <= 1e-3
+
+
+def test_attention_over_more_keys_than_one_launch_prepares():
+    """64 kv heads of 4.2 M tokens: K and V are more than 2^24 groups of 32 keys.  The heads overlap in memory (16
+    bytes apart), so that the inputs stay small; every query attends to its own block."""
+    H, T, d, b = 64, (1 << 22) + 64, 64, 64
+    N = T // b
+    need = 2 * H * T * d * 2
+    if torch.cuda.mem_get_info()[0] < need + (12 << 30):
+        pytest.skip(f"{need >> 30} GiB of workspace do not fit beside what is in use")
+    g = torch.Generator(device="cuda").manual_seed(6)
+    flat = [torch.randn(T * d + 8 * H, generator=g, device="cuda").to(torch.bfloat16) for _ in range(4)]
+    Q, K, V, O = (x.as_strided((H, T, d), (8, d, 1)) for x in flat)
+    idx = torch.arange(N, dtype=torch.int32, device="cuda").expand(H, N)[..., None].contiguous()
+    cnt = torch.ones((H, N), dtype=torch.int32, device="cuda")
+    out = dict(O=O, lse=torch.empty((H, T), device="cuda"), mass=torch.full((H, T), 7.0, device="cuda"))
+    print(f"[fullsize] preparation of {2 * H * T // 32} groups", flush=True)
+    a = binding.stream_sparse_attn(Q, K, V, H, H, b, idx, cnt, 0.125, want_lse=True, want_mass=True, out=out)
+    torch.cuda.synchronize()
+    causal = torch.ones(b, b, dtype=torch.bool, device="cuda").tril()
+    for h in (0, 31, 32, 63):
+        for q in (0, N // 2, N - 1):
+            rows = slice(q * b, q * b + b)
+            S = (Q[h, rows].float() @ K[h, rows].float().T * 0.125).masked_fill(~causal, -math.inf)
+            assert (a["lse"][h, rows] - S.logsumexp(1)).abs().max() <= 1e-3
+            assert (a["mass"][h, rows] - S.softmax(1).sum(0)).abs().max() <= 1e-3
