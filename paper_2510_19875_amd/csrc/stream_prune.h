@@ -59,6 +59,24 @@ __host__ __device__ __forceinline__ int variable_k(int valid, int num, int den, 
     return (int)(k > kmax ? kmax : k);
 }
 
+// Blocks a row keeps, on average over the rows: the k of its sequence (which topk_max may exceed by far), at most
+// the key blocks the mask can show it.  Variable k (vk_den > 0): twice what the longest rows keep, which last as
+// long as the launch and are few.
+inline long long mean_kept(const Problem &pb, const SeqTable &seqs, int vk_num, int vk_den, int vk_min)
+{
+    long long sum = 0, rows = 0;
+    for (int i = 0; i < seqs.n; ++i) {
+        const SeqDesc &sd = seqs.d[i];
+        const long long nkb = (long long)sd.nblk * pb.b / pb.bk;
+        long long most = nkb;
+        if (pb.mask == STREAM_MASK_SLIDING && ((long long)pb.window + pb.b) / pb.bk + 1 < most) most = ((long long)pb.window + pb.b) / pb.bk + 1;
+        const long long k = vk_den > 0 ? 2LL * variable_k((int)most, vk_num, vk_den, vk_min, pb.kmax) : sd.k;
+        sum += sd.nblk * (k < most ? k : most);
+        rows += sd.nblk;
+    }
+    return (sum + rows - 1) / rows;
+}
+
 constexpr int kWideTopk = 512;       // blocks kept per row by the wide kernel (node lists in LDS)
 
 // Runs every row's levels in one launch of the wide kernel (p.wide_ki selects the k of a sweep).

@@ -12,6 +12,7 @@
 // (stream_prune_multi) and a sparsity constant per row (stream_prune_variable).
 #include "stream_prune.h"
 
+#include <algorithm>
 #include <math.h>
 
 #include <mutex>
@@ -498,11 +499,14 @@ constexpr int kShortListTopk = 8;
 // 512 at 8 (fp32) 135 / 71, the other way round 2048 at 16 65 / 75, 3072 at 32 217 / 225.  In a sweep most values
 // of k find their scores in the cache: 1128 rows from k = 64 (blocks of 32) 110 / 95, from k = 32
 // (blocks of 64) 233 / 161, 2256 rows from 64 175 / 205.
-static bool few_rows(const Problem &pb, bool multi)
+// kept: blocks a row keeps (a sweep: for the largest value it visits).  By topk_max instead, rows with lists much shorter
+// than their slots were shared: 16 sequences of 640 tokens, 12/2 heads, k = 64 and fifteen times 1 28 / 52,
+// variable k of 1 to 64, 1 % of the blocks, 10 k tokens 46 / 73.
+static bool few_rows(const Problem &pb, bool multi, long long kept)
 {
     const long long rows = (long long)pb.H * pb.NB;
-    if (multi) return rows <= (pb.b == 32 ? 20LL : 40LL) * pb.kmax;
-    return rows <= (pb.b == 32 ? 80LL : 64LL) * pb.kmax;
+    if (multi) return rows <= (pb.b == 32 ? 20LL : 40LL) * kept;
+    return rows <= (pb.b == 32 ? 80LL : 64LL) * kept;
 }
 
 template <bool MULTI, bool BF16, int D, bool ARB>
@@ -607,7 +611,9 @@ static stream_status run_prune(const void *Q, const void *K, const stream_shape 
     const bool wide = pb.kmax > kMaxTopk;       // more than one node per lane: the LDS-list kernel
     if (wide && !level_wide_supported(pb)) return STREAM_EUNSUPPORTED;
     int wpr = 1;
-    bool split = few_rows(pb, multi);
+    long long kept = mean_kept(pb, pb.seqs, vk.num, vk.den, vk.kmin);
+    if (multi) kept = *std::max_element(topk_list, topk_list + n_k);
+    bool split = few_rows(pb, multi, kept);
     level_fn fn = wide ? nullptr : pick_level_kernel(pb, multi, split, wpr);
     if (!wide && !fn) return STREAM_EUNSUPPORTED;
     const PruneWorkspace w = prune_layout(pb);

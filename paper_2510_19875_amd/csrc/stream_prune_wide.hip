@@ -457,9 +457,11 @@ stream_status launch_level_wide(const Problem &pb, const PruneParams &p_in, hipS
     // Few rows: four wavefronts share one.  Four lists of nodes instead of two limit the workgroups a CU
     // holds, so a shared row has to pay early.  us, own row / shared row (blocks of 32): 1692 rows at k = 65
     // 122 / 64, 2628 at 80 171 / 106, 2628 at 200 190 / 105, the other way round 3840 at 70 181 / 187, 3840 at
-    // 256 196 / 234, 5628 at 100 332 / 351; blocks of 64: 3072 at 100 319 / 341.
+    // 256 196 / 234, 5628 at 100 332 / 351; blocks of 64: 3072 at 100 319 / 341.  Lists far shorter than their
+    // slots (a packed batch, variable k) as in the narrow kernel.
     const long long rows = (long long)pb.H * pb.NB;
-    bool split = rows <= (pb.b == 32 ? 3000 : 1500) && (size_t)4 * kWideWordsPerK * pb.kmax * 4 <= 65536;
+    const long long kept = mean_kept(pb, p_in.seqs, p_in.vk_num, p_in.vk_den, p_in.vk_min);
+    bool split = rows <= (pb.b == 32 ? 3000 : 1500) && rows <= (pb.b == 32 ? 80LL : 64LL) * kept && (size_t)4 * kWideWordsPerK * pb.kmax * 4 <= 65536;
     wide_fn fn = pick_wide_kernel(pb, split);
     if (!fn) return STREAM_EUNSUPPORTED;
     PruneParams p = p_in;
