@@ -126,8 +126,10 @@ struct AttnParams {
     const unsigned *cbits, *call;
     long long cpitch;
     int cw;
-    unsigned sweep;              // workgroups an XCD starts while a row walks its list (not SPLIT): see phase_sweep
+    unsigned sweep;              // workgroups an XCD starts while a row walks its list (rows of their own): see phase_sweep
     WgMap map;
+    WgMap map_own;               // few rows: the mapping with a row per wavefront
+    int share_from;              // few rows: entries in 64 lists at which sharing pays
     SeqTable seqs;
 };
 static_assert(sizeof(AttnParams) <= 4096, "kernel arguments are limited to 4 KB");
@@ -180,10 +182,10 @@ __device__ __forceinline__ float dot2_ones(unsigned pair, float acc)
 // One (head, query block, query sub-tile) row of the launch: what both passes derive from the
 // workgroup number, the sequence table and the row's list.
 // ARB: the mask C is an explicit bit array (STREAM_MASK_ARRAY).  WIDE: lists of more than 64 entries
-// (up to kMaxTopkWide) sit in LDS instead of one register.  SPLIT: the four wavefronts of a workgroup
-// share one row, wavefront w taking the sub-tiles w, w + 4, ... (else a wavefront has a row of its own).
-// SHIFT: the walk over the list is shifted (rows in phase, see attn_row).
-template <bool ARB, bool WIDE, bool SPLIT, bool SHIFT>
+// (up to kMaxTopkWide) sit in LDS instead of one register.  SHIFT: the walk over the list is shifted (rows in
+// phase, see attn_row).  A wavefront has a row of its own, or the four of a workgroup share one, wavefront w
+// taking the sub-tiles w, w + 4, ...
+template <bool ARB, bool WIDE, bool SHIFT>
 struct AttnRow {
     int lane, wave;
     int h, kvh, gb, q, L, qtok0, qt;            // head, kv head, global / local query block, length, first query, queries
@@ -240,10 +242,10 @@ struct AttnRow {
     }
 };
 
-// Fills in the row and issues the loads of its list; false: nothing to do.  (SPLIT: the same answer in all four
-// wavefronts.)
-template <bool ARB, bool WIDE, bool SPLIT, bool SHIFT>
-__device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, int *lds_list, AttnRow<ARB, WIDE, SPLIT, SHIFT> &r)
+// Fills in the row and issues the loads of its list; false: nothing to do.  (shared: the same answer in all
+// four wavefronts.)
+template <bool ARB, bool WIDE, bool SHIFT>
+__device__ __forceinline__ bool attn_row(const AttnParams &p, const WgMap &map, bool shared, int qt, int *lds_list, AttnRow<ARB, WIDE, SHIFT> &r)
 {
     r.lane = threadIdx.x & 63;
     r.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: keep it scalar
@@ -251,7 +253,7 @@ __device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, int *lds_l
     // compiler loads each where it is first used and waits for it there - a dozen round trips to
     // the scalar cache one after the other, at the start of every row.  (The empty asm makes them
     // live here.)
-    WgMap a_map = p.map;
+    WgMap a_map = map;
     int a_NB = p.NB, a_g = p.g, a_kmax = p.kmax, a_nseq = p.seqs.n, a_b = p.b, a_qsub = p.qsub;
     r.mask = p.mask; r.window = p.window; r.ksh = p.ksh;
     unsigned long long u_idx = (unsigned long long)p.idx, u_cnt = (unsigned long long)p.cnt;
@@ -266,7 +268,7 @@ __device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, int *lds_l
     int slot;
     if (!wg_decode(a_map, blockIdx.x, r.kvh, slot)) return false;
     const long long items_per_kv = (long long)a_NB * a_g * a_qsub;
-    const long long it = SPLIT ? (long long)slot : (long long)slot * 4 + r.wave;
+    const long long it = shared ? (long long)slot : (long long)slot * 4 + r.wave;
     if (it >= items_per_kv) return false;
     int qs, rk_blk, rk_head;
     if (items_per_kv <= 0x7fffffffLL) {           // (a 64-bit division is ~100 instructions)
@@ -305,8 +307,8 @@ __device__ __forceinline__ bool attn_row(const AttnParams &p, int qt, int *lds_l
 // Second half, after the kernel has issued its loads of Q: this waits for the list.  (In one piece the wait
 // came ahead of the loads of Q: pass 1 378 instead of 369 us at 10 k tokens and k = 256, pass 2 2.39 instead of
 // 2.37 ms at 131 k.)
-template <bool ARB, bool WIDE, bool SPLIT, bool SHIFT>
-__device__ __forceinline__ void attn_list(const AttnParams &p, AttnRow<ARB, WIDE, SPLIT, SHIFT> &r)
+template <bool ARB, bool WIDE, bool SHIFT>
+__device__ __forceinline__ void attn_list(const AttnParams &p, AttnRow<ARB, WIDE, SHIFT> &r)
 {
     __builtin_amdgcn_sched_barrier(0);
     const int a_kmax = r.kmax, a_b = r.bq, qt = r.qt, gb = r.gb, nblk = r.nblk;
@@ -396,11 +398,23 @@ __device__ __forceinline__ void attn_list(const AttnParams &p, AttnRow<ARB, WIDE
 // silently: a probability beyond 2^127 shows as a non-finite normaliser / output, and then the row is
 // computed again with the maximum tracked in every sub-tile (`safe`).
 //
-// SPLIT: for launches with too few rows to fill the chip; the wavefronts' partial results are merged
+// SPLIT: the four wavefronts share a row, in launches with too few rows to fill the chip; the wavefronts' partial results are merged
 // through LDS at the end.
 // ---------------------------------------------------------------------------------------------
-template <bool BF16, int D, int NQ, int OCC, bool ARB, bool WIDE, bool SPLIT>
-__global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
+template <bool BF16, int D, int NQ>
+struct FwdLds {
+    // staging of the output: 32 query rows of at most 256 bytes at a time (the pad of 16 bytes per row
+    // spreads the rows over the banks); partial results of shared rows are staged in fp32
+    static constexpr int ndbu(int es) { return D / 32 < 256 / (32 * es) ? D / 32 : 256 / (32 * es); }   // feature blocks per staged unit
+    static constexpr int row(int es) { return ndbu(es) * 32 * es; }
+    static constexpr int ES = BF16 ? 2 : 4;
+    static constexpr int Q = NQ == 1 ? 0 : NQ * D * ES / 32 * 1024;
+    static constexpr int bytes(bool few) { int o = 32 * (row(few ? 4 : ES) + 16); return Q > o ? Q : o; }   // per wavefront
+};
+
+template <bool BF16, int D, int NQ, bool ARB, bool WIDE, bool SPLIT, bool SHIFT>
+__device__ __forceinline__ void attn_fwd_rows(const AttnParams &p, const WgMap &map, char *s_q, int wave_lds,
+                                              int (*s_blk)[WIDE ? kMaxTopkWide : 1], float (*s_ml)[3][SPLIT ? 32 * NQ : 1])
 {
     constexpr int ES = BF16 ? 2 : 4;
     constexpr int FR = D * ES / 32;            // K/Q fragments per 32-token group
@@ -412,24 +426,16 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
     // 32-query rows: half the output accumulators, room for Q and for V fragments of their own (10 k
     // tokens, 12/2 heads, k = 64 / 256: 160 / 421 us with shared registers and Q in LDS, 158 / 409 us so)
     constexpr bool QREG = NQ == 1, OWNV = NQ == 1;
-    // staging of the output: 32 query rows of at most 256 bytes at a time (the pad of 16 bytes per row
-    // spreads the rows over the banks); partial results of SPLIT are staged in fp32
     constexpr int OES = SPLIT ? 4 : ES;
-    constexpr int O_NDBU = NDB < 256 / (32 * OES) ? NDB : 256 / (32 * OES);   // feature blocks per staged unit
-    constexpr int O_URB = O_NDBU * 32 * OES, O_URS = O_URB + 16;
-    constexpr int Q_LDS = QREG ? 0 : NQ * FR * 1024, O_LDS = 32 * O_URS;
-    constexpr int WAVE_LDS = Q_LDS > O_LDS ? Q_LDS : O_LDS;    // Q fragments, then the output staging
-    __shared__ __align__(16) char s_q[4][WAVE_LDS];
-    __shared__ int s_blk[WIDE ? 4 : 1][WIDE ? kMaxTopkWide : 1];
-    __shared__ float s_ml[SPLIT ? 4 : 1][3][SPLIT ? QT : 1];   // SPLIT: reference, sum, sum of rounded per query
+    constexpr int O_NDBU = FwdLds<BF16, D, NQ>::ndbu(OES), O_URB = FwdLds<BF16, D, NQ>::row(OES), O_URS = O_URB + 16;
 
-    AttnRow<ARB, WIDE, SPLIT, !SPLIT> r;
+    AttnRow<ARB, WIDE, SHIFT> r;
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (!attn_row(p, QT, s_blk[WIDE ? wave_id : 0], r)) return;
+    if (!attn_row(p, map, SPLIT, QT, s_blk[WIDE ? wave_id : 0], r)) return;
     const int lane = r.lane, wave = r.wave;
     const int col = lane & 31, gh = lane >> 5;
     const int L = r.L, qtok0 = r.qtok0;
-    char *my_lds = s_q[wave];
+    char *my_lds = s_q + wave * wave_lds;
     const unsigned lane_off = lane * 16;
 
     // packed K and V of this (kv head, sequence)
@@ -737,7 +743,7 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
                 for (int w = 0; w < 4; ++w)
 #pragma unroll
                     for (int e4 = 0; e4 < FPL / 4; ++e4) {
-                        const float4 v = *reinterpret_cast<const float4 *>(s_q[w] + rr * O_URS + ((lane % LPR) * FPL + e4 * 4) * 4);
+                        const float4 v = *reinterpret_cast<const float4 *>(s_q + w * wave_lds + rr * O_URS + ((lane % LPR) * FPL + e4 * 4) * 4);
                         o[e4 * 4 + 0] += v.x; o[e4 * 4 + 1] += v.y; o[e4 * 4 + 2] += v.z; o[e4 * 4 + 3] += v.w;
                     }
                 if (tok < L) {
@@ -819,19 +825,17 @@ __global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
 // rq*32 + 8*(i/4) + 4*gh + (i%4).  No output accumulators: Q stays in registers, two wavefronts per
 // SIMD so that one's exponentials overlap the other's MFMAs.
 // ---------------------------------------------------------------------------------------------
-template <bool BF16, int D, int NQ, int OCC, bool ARB, bool WIDE, bool SPLIT>
-__global__ void __launch_bounds__(256, OCC) attn_mass_kernel(const AttnParams p)
+template <bool BF16, int D, int NQ, bool ARB, bool WIDE, bool SHIFT>
+__device__ __forceinline__ void attn_mass_rows(const AttnParams &p, const WgMap &map, bool shared, int (*s_blk)[WIDE ? kMaxTopkWide : 1])
 {
     constexpr int ES = BF16 ? 2 : 4;
     constexpr int FR = D * ES / 32;
     constexpr int QT = 32 * NQ;
     constexpr int GROUP_BYTES = 32 * D * ES;
-    constexpr int TS = SPLIT ? 4 : 1;
-    __shared__ int s_blk[WIDE ? 4 : 1][WIDE ? kMaxTopkWide : 1];
-
-    AttnRow<ARB, WIDE, SPLIT, !SPLIT && NQ == 1> r;        // (64-query rows gain nothing from a shift here)
+    const int TS = shared ? 4 : 1;
+    AttnRow<ARB, WIDE, SHIFT> r;
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (!attn_row(p, QT, s_blk[WIDE ? wave_id : 0], r)) return;
+    if (!attn_row(p, map, shared, QT, s_blk[WIDE ? wave_id : 0], r)) return;
     const int lane = r.lane;
     const int col = lane & 31, gh = lane >> 5;
     const int L = r.L, qtok0 = r.qtok0;
@@ -873,7 +877,7 @@ __global__ void __launch_bounds__(256, OCC) attn_mass_kernel(const AttnParams p)
     }
     attn_list(p, r);
     float *mass_h = p.mass + (long long)r.h * p.T + r.tok0;
-    const int n_tiles = r.n_tiles, t0 = SPLIT ? r.wave : 0;
+    const int n_tiles = r.n_tiles, t0 = shared ? r.wave : 0;
     uint4 kreg[FR];
     if (t0 < n_tiles) {
         const unsigned off0 = (unsigned)r.group(t0, r.fetch(t0)) * (unsigned)GROUP_BYTES;
@@ -946,6 +950,52 @@ __global__ void __launch_bounds__(256, OCC) attn_mass_kernel(const AttnParams p)
     }
 }
 
+// Do the lists of a launch pay for sharing the rows?  Every wavefront looks at the same 64 counts, spread over
+// the launch, and comes to the same answer.  (The host knows the slots of the lists only: a sweep's or a packed
+// batch's may be nearly empty.)
+__device__ __forceinline__ bool share_rows(const AttnParams &p)
+{
+    const long long total = (long long)p.H * p.NB;
+    const int most = p.kmax;
+    const int c = min(max(p.cnt[total * (threadIdx.x & 63) >> 6], 0), most);
+    return __builtin_amdgcn_readfirstlane((int)wave_sum((float)c)) >= p.share_from;
+}
+
+// Who works on a row: its own wavefront, the four of a workgroup, or as the lists say.
+enum AttnMode { kOwnRow = 0, kSharedRow = 1, kByLists = 2 };
+
+template <bool BF16, int D, int NQ, int OCC, bool ARB, bool WIDE, int MODE>
+__global__ void __launch_bounds__(256, OCC) attn_fwd_kernel(const AttnParams p)
+{
+    constexpr int WAVE_LDS = FwdLds<BF16, D, NQ>::bytes(MODE != kOwnRow);     // Q fragments, then the output staging
+    __shared__ __align__(16) char s_q[4 * WAVE_LDS];
+    __shared__ int s_blk[WIDE ? 4 : 1][WIDE ? kMaxTopkWide : 1];
+    if constexpr (MODE == kOwnRow) {
+        attn_fwd_rows<BF16, D, NQ, ARB, WIDE, false, true>(p, p.map, s_q, WAVE_LDS, s_blk, nullptr);
+    } else {
+        __shared__ float s_ml[4][3][32 * NQ];                     // reference, sum, sum of rounded per query
+        if (MODE == kSharedRow || share_rows(p))
+            attn_fwd_rows<BF16, D, NQ, ARB, WIDE, true, false>(p, p.map, s_q, WAVE_LDS, s_blk, s_ml);
+        else if ((int)blockIdx.x < p.map_own.grid)
+            attn_fwd_rows<BF16, D, NQ, ARB, WIDE, false, false>(p, p.map_own, s_q, WAVE_LDS, s_blk, nullptr);
+    }
+}
+
+template <bool BF16, int D, int NQ, int OCC, bool ARB, bool WIDE, int MODE>
+__global__ void __launch_bounds__(256, OCC) attn_mass_kernel(const AttnParams p)
+{
+    __shared__ int s_blk[WIDE ? 4 : 1][WIDE ? kMaxTopkWide : 1];
+    if constexpr (MODE == kOwnRow) {
+        attn_mass_rows<BF16, D, NQ, ARB, WIDE, NQ == 1>(p, p.map, false, s_blk);        // (64-query rows gain nothing from a shift here)
+    } else if constexpr (MODE == kSharedRow) {
+        attn_mass_rows<BF16, D, NQ, ARB, WIDE, false>(p, p.map, true, s_blk);
+    } else {
+        const bool shared = share_rows(p);
+        if (!shared && (int)blockIdx.x >= p.map_own.grid) return;
+        attn_mass_rows<BF16, D, NQ, ARB, WIDE, false>(p, shared ? p.map : p.map_own, shared, s_blk);
+    }
+}
+
 typedef void (*attn_fn)(const AttnParams);
 
 // A kernel and the workgroups of it that a CU runs at a time.
@@ -1013,34 +1063,36 @@ static AttnKernel attn_kernel() { return AttnKernel{FN, attn_per_cu<FN>}; }
 // Wavefronts own 64 queries of a row (32 for query block 32).  fp32 with d = 128 fits one wavefront per
 // SIMD only.
 template <bool BF16, int D, int NQ, bool ARB, bool WIDE>
-static AttnKernel pick_attn(int pass, bool split)
+static AttnKernel pick_attn(int pass, AttnMode mode)
 {
     constexpr int OCC = BF16 || D == 64 ? 2 : 1;
     if (pass == 1)
-        return split ? attn_kernel<attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, true>>()
-                     : attn_kernel<attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, false>>();
-    return split ? attn_kernel<attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, true>>()
-                 : attn_kernel<attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, false>>();
+        return mode == kOwnRow      ? attn_kernel<attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, kOwnRow>>()
+               : mode == kSharedRow ? attn_kernel<attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, kSharedRow>>()
+                                    : attn_kernel<attn_fwd_kernel<BF16, D, NQ, OCC, ARB, WIDE, kByLists>>();
+    return mode == kOwnRow      ? attn_kernel<attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, kOwnRow>>()
+           : mode == kSharedRow ? attn_kernel<attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, kSharedRow>>()
+                                : attn_kernel<attn_mass_kernel<BF16, D, NQ, OCC, ARB, WIDE, kByLists>>();
 }
 
 template <bool BF16, int D, int NQ>
-static AttnKernel pick_attn_list(int pass, bool split, bool arb, bool wide)
+static AttnKernel pick_attn_list(int pass, AttnMode mode, bool arb, bool wide)
 {
-    if (arb) return wide ? pick_attn<BF16, D, NQ, true, true>(pass, split) : pick_attn<BF16, D, NQ, true, false>(pass, split);
-    return wide ? pick_attn<BF16, D, NQ, false, true>(pass, split) : pick_attn<BF16, D, NQ, false, false>(pass, split);
+    if (arb) return wide ? pick_attn<BF16, D, NQ, true, true>(pass, mode) : pick_attn<BF16, D, NQ, true, false>(pass, mode);
+    return wide ? pick_attn<BF16, D, NQ, false, true>(pass, mode) : pick_attn<BF16, D, NQ, false, false>(pass, mode);
 }
 
-static AttnKernel pick_attn_kernel(const Problem &pb, int pass, bool split)
+static AttnKernel pick_attn_kernel(const Problem &pb, int pass, AttnMode mode)
 {
     const bool arb = pb.mask == STREAM_MASK_ARRAY;
     const bool wide = pb.kmax > kMaxTopk;              // lists longer than one register of entries
     const bool nq1 = pb.b == 32;
     if (pb.dtype == STREAM_BF16) {
-        if (pb.d == 128) return nq1 ? pick_attn_list<true, 128, 1>(pass, split, arb, wide) : pick_attn_list<true, 128, 2>(pass, split, arb, wide);
-        return nq1 ? pick_attn_list<true, 64, 1>(pass, split, arb, wide) : pick_attn_list<true, 64, 2>(pass, split, arb, wide);
+        if (pb.d == 128) return nq1 ? pick_attn_list<true, 128, 1>(pass, mode, arb, wide) : pick_attn_list<true, 128, 2>(pass, mode, arb, wide);
+        return nq1 ? pick_attn_list<true, 64, 1>(pass, mode, arb, wide) : pick_attn_list<true, 64, 2>(pass, mode, arb, wide);
     }
-    if (pb.d == 128) return nq1 ? pick_attn_list<false, 128, 1>(pass, split, arb, wide) : pick_attn_list<false, 128, 2>(pass, split, arb, wide);
-    return nq1 ? pick_attn_list<false, 64, 1>(pass, split, arb, wide) : pick_attn_list<false, 64, 2>(pass, split, arb, wide);
+    if (pb.d == 128) return nq1 ? pick_attn_list<false, 128, 1>(pass, mode, arb, wide) : pick_attn_list<false, 128, 2>(pass, mode, arb, wide);
+    return nq1 ? pick_attn_list<false, 64, 1>(pass, mode, arb, wide) : pick_attn_list<false, 64, 2>(pass, mode, arb, wide);
 }
 
 // When the four wavefronts of a workgroup share one row: few rows, per sub-tile of a full list, and for
@@ -1051,7 +1103,10 @@ static AttnKernel pick_attn_kernel(const Problem &pb, int pass, bool split)
 // 2256 x 64 166 / 152; the other way round 1536 x 16 54.8 / 55.5, 1024 x 16 (fp32, d = 64) 131 / 135,
 // 2048 x 32 122 / 140, 3072 x 16 77 / 92.  At 3756 rows x 64 and 3840 x 256 pass 1 is 158 / 163 and 409 /
 // 445, pass 2 101 / 102 and 279 / 264.
-constexpr long long kSplitRowsPerTile = 60, kSplitRows = 3000;
+// The host knows the slots of the lists; from kShareAlways rows on the kernels go by the lists themselves
+// (share_rows), whose mean lies below the slots also where they are full (the first rows of a sequence).  By the slots alone, 64 of them holding 1 entry: pass 1 of 1500 rows 26.7 us instead of 16.0, of
+// 3000 rows 42.6 instead of 22.9; 756 rows of 16 slots 18.8 either way.
+constexpr long long kSplitRowsPerTile = 60, kSplitRows = 3000, kShareAlways = 800, kShareRowsPerTile = 84;
 
 struct AttnWorkspace {
     size_t kp, vp, lse2, cany, call, total;
@@ -1169,7 +1224,9 @@ stream_status stream_sparse_attn(const void *Q, const void *K, const void *V,
         const long long per_kv = split ? items_per_kv : (items_per_kv + 3) / 4;
         if (per_kv * pb.Hkv + 64 > 0x7fffffffLL) return STREAM_EUNSUPPORTED;
         p.map = make_wg_map(pb.Hkv, (int)per_kv);
-        const AttnKernel k = pick_attn_kernel(pb, pass, split);
+        p.map_own = make_wg_map(pb.Hkv, (int)((items_per_kv + 3) / 4));
+        p.share_from = (int)((rows * 64 + (kShareRowsPerTile << p.ksh) - 1) / (kShareRowsPerTile << p.ksh));
+        const AttnKernel k = pick_attn_kernel(pb, pass, split ? (rows <= kShareAlways ? kSharedRow : kByLists) : kOwnRow);
         const bool one = pass == 1 && !split && one_wg_per_cu(pb, topk_max);
         p.sweep = split ? 1u : phase_sweep(pb.dtype == STREAM_BF16, one ? 1 : k.per_cu(), p.map.grid);
         hipLaunchKernelGGL(k.fn, dim3((unsigned)p.map.grid), dim3(256), one ? kOneWgPerCuLds : 0u, st, p);

@@ -120,3 +120,44 @@ def test_steep_scores(block, dtype, d, n_sub):
             assert np.abs(O - ref["O"]).max() <= TOL[dtype]
             assert np.abs(lse - ref["lse"]).max() <= 1e-3
             assert (np.abs(mass - ref["mass"]) / np.maximum(ref["mass"], 1.0)).max() <= 1e-3
+
+
+@pytest.mark.parametrize("T,block,k,slots,dtype,d,mask", [
+    (1013, 32, 1, 64, "bf16", 128, "causal"),      # nearly empty lists: a row per wavefront after all
+    (1013, 32, 32, 64, "bf16", 128, "causal"),     # full ones: shared
+    (1990, 64, 2, 30, "bf16", 64, "sliding"),
+    (1990, 64, 16, 30, "f32", 64, "causal"),
+    (2000, 128, 1, 16, "bf16", 128, "documents"),
+    (1111, 64, 17, 20, "f32", 128, "documents"),
+    (2300, 32, 2, 66, "bf16", 128, "causal"),
+    (2300, 32, 66, 70, "bf16", 64, "documents"),
+])
+def test_few_rows_go_by_their_lists(T, block, k, slots, dtype, d, mask):
+    """Lists of k entries in `slots` slots, rows enough that the lists decide who shares."""
+    w = wl.scaled(wl.config(2), (T,), topk=k, heads=1, kv_heads=1, block=block, dtype=dtype, head_dim=d,
+                  needles_per_kv_head=2)
+    Q, K, V, _ = wl.make_inputs(w)
+    C = documents(T) if mask == "documents" else None
+    rule = dict(mask="sliding", window=150) if mask == "sliding" else {}
+    ref_kw = dict(C=C.astype(np.uint8)) if C is not None else rule
+    Qf, Kf, Vf = Q.float().numpy(), K.float().numpy(), V.float().numpy()
+    lists = so.prune(Qf, Kf, 1, 1, block, k, **ref_kw)
+    scale = 1.0 / math.sqrt(d)
+    ref = so.sparse_attn(Qf, Kf, Vf, 1, 1, block, lists["idx"], lists["cnt"], scale, **ref_kw)
+    rows = -(-T // block) * (2 if block == 128 else 1)
+    n = 800 // rows + 1
+    assert 800 < n * rows <= min(3000, 60 * slots * max(1, block // 32))
+    idx = np.full((1, lists["idx"].shape[1], slots), -1, np.int32)
+    idx[:, :, :k] = lists["idx"]
+    print(f"[split] T={T} b={block} k={k} of {slots} {dtype} {mask} heads={n}", flush=True)
+    rep = lambda x: x.to(DEV).expand(n, -1, -1).contiguous()
+    cnt = torch.from_numpy(lists["cnt"]).to(DEV).expand(n, -1).contiguous()
+    a = binding.stream_sparse_attn(rep(Q), rep(K), rep(V), n, n, block, rep(torch.from_numpy(idx)), cnt, scale, want_lse=True,
+                                   want_mass=True, **(dict(mask_bits=bits_of(C)) if C is not None else rule))
+    torch.cuda.synchronize()
+    O, lse, mass = (a[x].float().cpu().numpy() for x in ("O", "lse", "mass"))
+    assert np.abs(O - ref["O"]).max() <= TOL[dtype]
+    np.testing.assert_array_equal(np.isneginf(lse), np.broadcast_to(np.isneginf(ref["lse"]), lse.shape))
+    seen = ~np.isneginf(ref["lse"][0])
+    assert np.abs(lse[:, seen] - ref["lse"][:, seen]).max() <= 1e-3
+    assert (np.abs(mass - ref["mass"]) / np.maximum(ref["mass"], 1.0)).max() <= 1e-3
