@@ -1,8 +1,8 @@
 // stream_sparse_attn: Eq. (2) of the paper on the retained key blocks, gfx950.
 //
 // A wavefront owns up to 64 query tokens of one (head, query block) and walks the block's
-// retained key blocks in list order, from a place of its own on and around the end; where rows are few
-// the four wavefronts of a workgroup share a row.  K tiles come from the same
+// retained key blocks: the first 32 keys of the list, then the rest in order from a place of its own on
+// and around the end; where rows are few the four wavefronts of a workgroup share a row.  K tiles come from the same
 // packed layout the pruning kernels use; V tiles are packed transposed so that a lane's 16
 // bytes hold one feature of the 8 (bf16) or 4 (fp32) keys its MFMA contraction slots cover.
 //
@@ -1104,8 +1104,9 @@ static AttnKernel pick_attn_kernel(const Problem &pb, int pass, AttnMode mode)
 // 2048 x 32 122 / 140, 3072 x 16 77 / 92.  At 3756 rows x 64 and 3840 x 256 pass 1 is 158 / 163 and 409 /
 // 445, pass 2 101 / 102 and 279 / 264.
 // The host knows the slots of the lists; from kShareAlways rows on the kernels go by the lists themselves
-// (share_rows), whose mean lies below the slots also where they are full (the first rows of a sequence).  By the slots alone, 64 of them holding 1 entry: pass 1 of 1500 rows 26.7 us instead of 16.0, of
-// 3000 rows 42.6 instead of 22.9; 756 rows of 16 slots 18.8 either way.
+// (share_rows; 84 instead of 60, since the mean lies below the slots also where the lists are full: the first
+// rows of a sequence).  By the slots alone, 64 of them holding 1 entry, pass 1 took 26.5 us instead of 16.1 for
+// 1500 rows and 42.5 instead of 24.2 for 3000; 756 rows of 16 slots 18.8 either way.
 constexpr long long kSplitRowsPerTile = 60, kSplitRows = 3000, kShareAlways = 800, kShareRowsPerTile = 84;
 
 struct AttnWorkspace {

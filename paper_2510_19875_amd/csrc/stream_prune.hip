@@ -499,9 +499,9 @@ constexpr int kShortListTopk = 8;
 // 512 at 8 (fp32) 135 / 71, the other way round 2048 at 16 65 / 75, 3072 at 32 217 / 225.  In a sweep most values
 // of k find their scores in the cache: 1128 rows from k = 64 (blocks of 32) 110 / 95, from k = 32
 // (blocks of 64) 233 / 161, 2256 rows from 64 175 / 205.
-// kept: blocks a row keeps (a sweep: for the largest value it visits).  By topk_max instead, rows with lists much shorter
-// than their slots were shared: 16 sequences of 640 tokens, 12/2 heads, k = 64 and fifteen times 1 28 / 52,
-// variable k of 1 to 64, 1 % of the blocks, 10 k tokens 46 / 73.
+// kept: blocks a row keeps (a sweep: for the largest value it visits).  By topk_max instead, rows with lists
+// much shorter than their slots were shared: 16 sequences of 640 tokens, 12/2 heads, k = 64 and fifteen times 1
+// 28 / 52, variable k of 1 to 64, 1 % of the blocks, 10 k tokens 46 / 73.
 static bool few_rows(const Problem &pb, bool multi, long long kept)
 {
     const long long rows = (long long)pb.H * pb.NB;

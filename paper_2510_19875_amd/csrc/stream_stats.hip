@@ -502,9 +502,9 @@ struct StatsWorkspace {
     int chunk;                   // query blocks per chunk
 };
 
-// Workgroups of the row kernel that the chip holds: 2 wavefronts per SIMD; 3 with 32 queries each (but an array
-// and 128 bytes or more a row take the registers of the third), 1 with fp32 at d = 128.  32 k tokens, 32/8
-// heads: rows 4.40 ms (1.0 PFLOP/s
+// Workgroups of the row kernel that the chip holds: 2 wavefronts per SIMD; 3 with 32 queries each (not with an
+// array and rows of more than 128 bytes, which take the registers of the third); 1 with fp32 at d = 128.
+// 32 k tokens, 32/8 heads: rows 4.40 ms (1.0 PFLOP/s
 // of scores), columns 74 us; two thirds of that time are what the MFMAs alone take at the clock the power
 // limit leaves (0.64 us per tile and SIMD, 0.92-0.97 with the exponentials and nothing else, 1.07 here).
 static int stats_wgs(const Problem &pb)
