@@ -129,7 +129,7 @@ struct AttnParams {
     unsigned sweep;              // workgroups an XCD starts while a row walks its list (rows of their own): see phase_sweep
     WgMap map;
     WgMap map_own;               // few rows: the mapping with a row per wavefront
-    int share_from;              // few rows: entries in 64 lists at which sharing pays
+    int share_from;              // few rows: entries at which sharing pays, 64 times the mean of a list
     SeqTable seqs;
 };
 static_assert(sizeof(AttnParams) <= 4096, "kernel arguments are limited to 4 KB");
@@ -950,14 +950,14 @@ __device__ __forceinline__ void attn_mass_rows(const AttnParams &p, const WgMap 
     }
 }
 
-// Do the lists of a launch pay for sharing the rows?  Every wavefront looks at the same 64 counts, spread over
-// the launch, and comes to the same answer.  (The host knows the slots of the lists only: a sweep's or a packed
-// batch's may be nearly empty.)
+// Do the lists of a launch pay for sharing the rows?  Every wavefront looks at the same 16 counts, spread over
+// the heads and over the length of the sequences, and comes to the same answer.  (The host knows the slots of
+// the lists only: a sweep's or a packed batch's may be nearly empty.)
 __device__ __forceinline__ bool share_rows(const AttnParams &p)
 {
-    const long long total = (long long)p.H * p.NB;
-    const int most = p.kmax;
-    const int c = min(max(p.cnt[total * (threadIdx.x & 63) >> 6], 0), most);
+    const int s = threadIdx.x & 15, most = p.kmax;
+    const long long h = ((long long)p.H * s) >> 4, q = (2LL * ((s * 7) & 15) + 1) * p.NB >> 5;
+    const int c = min(max(p.cnt[h * p.NB + q], 0), most);
     return __builtin_amdgcn_readfirstlane((int)wave_sum((float)c)) >= p.share_from;
 }
 
