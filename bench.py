@@ -622,8 +622,8 @@ def block_shapes(w, layer, scale, reps=3):
 
 
 def receiver_stats(w, layer, scale, reps=2):
-    """stream_receiver_stats on the same Q, K: two dense passes of b x b x d tile products over the
-    causal half of the pattern (row log-sum-exp, then block means and column moments)."""
+    """stream_receiver_stats on the same Q, K: the b x b x d tile products over the causal half of the
+    pattern, each once (sums of exponentials per span, then block means and column moments)."""
     import torch
 
     from paper_2510_19875_amd import binding
@@ -647,7 +647,7 @@ def receiver_stats(w, layer, scale, reps=2):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / reps
     N = w.blocks_per_seq[0]
-    flop = 2.0 * w.heads * (N * (N + 1) / 2) * 2.0 * w.block * w.block * w.head_dim
+    flop = w.heads * (N * (N + 1) / 2) * 2.0 * w.block * w.block * w.head_dim
     return {"ms": ms, "tflops": flop / (ms * 1e-3) / 1e12, "bound": "mfma",
             "frac_of_mfma_peak": flop / (ms * 1e-3) / 1e12 / mfma_peak(w.dtype),
             "max_column_kurtosis_head0": float(st["out"]["head"][0, 0, 0].item())}
